@@ -28,8 +28,7 @@
 // (O, max, sum) a combine kernel merges in a fixed order, so results do not
 // depend on timing.
 //
-// Generic path: one wavefront per (row, query head), float32 arithmetic, any
-// head_dim <= 512 and either storage dtype.
+// Every other geometry goes to the generic kernel (generic_attention.hip).
 #include <math.h>
 
 #include <algorithm>
@@ -1245,103 +1244,6 @@ __global__ __launch_bounds__(256) void sel_attn_combine(const AttnArgs a) {
   if (a.lse && d16 == 0) a.lse[((int64_t)layer * a.Hq + h) * a.n_sel + m] = (M + __log2f(Lsum)) * kLn2;
 }
 
-// ============================================================== generic attention
-struct GenAttnArgs {
-  const void* q;
-  const int32_t* sel;
-  void* out;
-  float* lse;
-  int64_t T, n, n_sel;
-  int cs1, Hq, Hkv, G, D, lb;
-  int q_by_slot;
-  float scale;
-};
-
-template <typename E>
-__device__ __forceinline__ float gld(const E* p);
-template <>
-__device__ __forceinline__ float gld<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float gld<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
-template <typename E>
-__device__ __forceinline__ void gst(E* p, float x);
-template <>
-__device__ __forceinline__ void gst<float>(float* p, float x) { *p = x; }
-template <>
-__device__ __forceinline__ void gst<uint16_t>(uint16_t* p, float x) { *p = f32_to_bf16(x); }
-
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o; o >>= 1) x += __shfl_xor(x, o);
-  return x;
-}
-
-template <typename E, typename Rows>
-__global__ __launch_bounds__(64) void sel_attn_generic(const GenAttnArgs a, const Rows rows) {
-  __shared__ float qs[512];
-  __shared__ float ps[64];
-  const int64_t m = blockIdx.x;
-  const int h = blockIdx.y;
-  const int layer = a.lb + blockIdx.z;
-  const int lane = threadIdx.x;
-  const int t = a.sel[m];
-  if (t < a.cs1 || t >= a.T) return;  // out-of-contract index
-  const int kv = h / a.G;
-  const E* qp = (const E*)a.q + (a.q_by_slot ? ((int64_t)blockIdx.z * a.Hq + h) * a.n_sel + m
-                                             : ((int64_t)layer * a.Hq + h) * a.n + (t - a.cs1)) * a.D;
-  const int64_t plane = (int64_t)layer * a.Hkv + kv;
-  const int rb = a.D * (int)sizeof(E);
-  for (int d = lane; d < a.D; d += 64) qs[d] = gld(qp + d);
-  __syncthreads();
-  float acc[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-  float mrun = -INFINITY, lrun = 0.f;
-  for (int j0 = 0; j0 <= t; j0 += 64) {
-    const int j = j0 + lane;
-    float s = -INFINITY;
-    if (j <= t) {
-      const E* kr = (const E*)rows.row(false, plane, j, rb);
-      float dot = 0.f;
-      for (int d = 0; d < a.D; ++d) dot = fmaf(qs[d], gld(kr + d), dot);
-      s = dot * a.scale;
-    }
-    const float m_new = fmaxf(mrun, wave_max(s));
-    const float alpha = mrun == -INFINITY ? 0.f : expf(mrun - m_new);
-    const float p = j <= t ? expf(s - m_new) : 0.f;
-    lrun = lrun * alpha + wave_sum(p);
-#pragma unroll
-    for (int x = 0; x < 8; ++x) acc[x] *= alpha;
-    ps[lane] = p;
-    __syncthreads();
-    const int cnt = min(64, t + 1 - j0);
-    for (int jj = 0; jj < cnt; ++jj) {
-      const float pj = ps[jj];
-      const E* vr = (const E*)rows.row(true, plane, j0 + jj, rb);
-#pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        const int d = lane + 64 * x;
-        if (d < a.D) acc[x] = fmaf(pj, gld(vr + d), acc[x]);
-      }
-    }
-    __syncthreads();
-    mrun = m_new;
-  }
-  E* op = (E*)a.out + (((int64_t)layer * a.Hq + h) * a.n_sel + m) * a.D;
-  const float inv = 1.f / lrun;
-#pragma unroll
-  for (int x = 0; x < 8; ++x) {
-    const int d = lane + 64 * x;
-    if (d < a.D) gst(op + d, acc[x] * inv);
-  }
-  if (a.lse && lane == 0) a.lse[((int64_t)layer * a.Hq + h) * a.n_sel + m] = mrun + logf(lrun);
-}
-
 // ============================================================== planning & launch
 static int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
@@ -1470,19 +1372,6 @@ static cs_status launch_mfma(int G, const AttnArgs& a, const Rows& rows, const S
   return CS_OK;
 }
 
-template <typename Rows>
-static void launch_generic(const Geo& g, const GenAttnArgs& a, const Rows& rows, int64_t n_sel, int layers,
-                           hipStream_t s) {
-  static_assert(sizeof(GenAttnArgs) + sizeof(Rows) <= 4096, "kernel arguments within 4 KB");
-  TraceScope tr("sel_attn_generic", s);
-  if (g.dtype == CS_BF16)
-    CS_LAUNCH(tr, (sel_attn_generic<uint16_t, Rows>), dim3((unsigned)n_sel, g.Hq, layers), dim3(64), 0, s, a,
-                       rows);
-  else
-    CS_LAUNCH(tr, (sel_attn_generic<float, Rows>), dim3((unsigned)n_sel, g.Hq, layers), dim3(64), 0, s, a,
-                       rows);
-}
-
 size_t rope_table_bytes(int64_t n_sel) { return ((size_t)n_sel * 64 * sizeof(float2) + 255) / 256 * 256; }
 
 bool chunks_tile_aligned(const Geo& g) {
@@ -1551,31 +1440,13 @@ cs_status launch_attention(const Geo& g, const AttnPlan& p, const CacheView& cv,
     if (st) return st;
     return check_launch("selective attention launch");
   }
-  GenAttnArgs a;
-  a.q = qf;
-  a.q_by_slot = q_by_slot ? 1 : 0;
-  a.sel = sel;
-  a.out = out;
-  a.lse = lse;
-  a.T = g.T;
-  a.n = g.n;
-  a.n_sel = n_sel;
-  a.cs1 = (int)g.cs1;
-  a.Hq = g.Hq;
-  a.Hkv = g.Hkv;
-  a.G = g.G;
-  a.D = g.D;
-  a.lb = lb;
-  a.scale = (float)(1.0 / sqrt((double)g.D));
-  const cs_status stg = check_grid(n_sel, g.Hq, layers, 64, "selective attention");
+  const cs_status stg = launch_attention_generic(g, cv, lb, le, sel, n_sel, qf, q_by_slot, out, lse, s, true);
   if (stg || check_only) return stg;
   if (job) {  // the scatter first: the attention reads the repaired rows
     if (cv.paged) launch_scatter_rows(sa, cv.pages<kMaxPages>(g), s);
     else launch_scatter_rows(sa, cv.flat(g), s);
   }
-  if (cv.paged) launch_generic(g, a, cv.pages<kMaxPages>(g), n_sel, layers, s);
-  else launch_generic(g, a, cv.flat(g), n_sel, layers, s);
-  return check_launch("generic attention launch");
+  return launch_attention_generic(g, cv, lb, le, sel, n_sel, qf, q_by_slot, out, lse, s, false);
 }
 
 }  // namespace cs

@@ -300,6 +300,10 @@ cs_status launch_attention(const Geo& g, const AttnPlan& plan, const CacheView& 
                            int lb, int le, const int32_t* sel, int64_t n_sel, const void* qf,
                            bool q_by_slot, void* out, float* lse, void* ws, hipStream_t s, bool check_only = false,
                            const ScatterJob* job = nullptr, const RopeJob* rope = nullptr);
+// Attention of every other geometry (any head_dim, either dtype; needs no workspace).
+cs_status launch_attention_generic(const Geo& g, const CacheView& cv, int lb, int le, const int32_t* sel,
+                                   int64_t n_sel, const void* qf, bool q_by_slot, void* out, float* lse,
+                                   hipStream_t s, bool check_only);
 cs_status launch_rope_scatter(const Geo& g, const CacheView& cv, int lb, int le, const int32_t* sel, int64_t n_sel,
                               const void* q_pre, const void* k_pre, const void* v_new, const int32_t* coords,
                               const double* theta, void* q_ws, hipStream_t s, bool check_only = false);
