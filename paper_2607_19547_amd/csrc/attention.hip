@@ -121,7 +121,15 @@ constexpr int kQPerWG = 32 * kWaves;     // query vectors per workgroup
 constexpr int kRow = 256;                // bytes of one K/V row (bf16 x 128)
 constexpr int kHiLds = 65536;            // LDS bytes below the K ring (the V ring)
 constexpr float kLn2 = 0.69314718055994530942f;
-constexpr float kRescaleLog2 = 8.0f;     // lazy rescale threshold (max growth 2^8)
+// Lazy rescale threshold: the max may grow by 2^5 before the accumulators are
+// rescaled.  A row that one key dominates has that key's bf16 rounding in its
+// sum unless the key became the running max itself (weight exactly 1), so the
+// threshold bounds how much a key can stand out unrescaled.  Ordinary rows grow
+// by less than 2^4 after their first tile; with 2^3 and 2^4 the rescales that
+// remain cost 1.3 and 0.6% at 32,768 tokens, rho = 1.  (Mean-square error of the
+// log-sum-exp of a 65,536-token layer over eight seeds: 2.3e-6 with 2^8, 2.0e-6
+// with 2^4.)
+constexpr float kRescaleLog2 = 5.0f;
 
 struct AttnArgs {
   const uint16_t* q;
@@ -135,7 +143,7 @@ struct AttnArgs {
   int cs1, Hq, Hkv, lb, layers;
   int part_cap;      // partial slots per layer
   int q_by_slot;     // q is [layers in call][H_q][n_sel][128] (rows in selection order), else [L][H_q][n][128]
-  int desc_off;      // item descriptors in the plan (set by the planning kernel's caller)
+  int desc_off;      // piece descriptors in the plan (set by the planning kernel's caller)
   const float2* rope_tab;  // [n_sel][64] cos/sin of the selected tokens: q holds pre-rotary queries, rotated on
                            // load; NULL: q is already rotated
   float scale_log2;  // log2(e) / sqrt(D)
@@ -226,14 +234,36 @@ constexpr int kMaxPieces = 2048;     // most pieces of a row tile (the piece siz
 constexpr int kPlanLdsPieces = kMaxPieces + 1;
 constexpr int kPlanSortCap = 2048;   // longest tail (a quarter of a queue) the plan reorders
 constexpr int kXcds = 8;
+// Runs.  An item of the attention launch is a run of `r` consecutive pieces of
+// one row tile for one KV head: the workgroup carries its running max, sum and
+// output through them and leaves one partial (none at all when the run covers
+// the row tile).  The plan picks r, from the pieces' lengths alone, to end the
+// launch soonest: few long items leave little to merge and few prologues and
+// epilogues (an item's fixed cost is about kItemCost key tiles), but must
+// share out evenly over the CUs.  The estimate (plan_body) follows a model of
+// the launch that reproduces the measured order of the candidates; best about
+// one item per CU for a layer of up to 200 key tiles per CU, two to four beyond
+// that (kMaxRun: longer items leave CUs idle at the end; 65,536 tokens at rho =
+// 0.1: 1,459 us a layer with items of 281 tiles, 1,497 with 138, 1,506 with
+// 908).  Measured for one layer, 16 query heads, against r = 1: 32,768 tokens at
+// rho = 0.05 213-228 us against 259, 16,384 at 0.1 117-128 against 148, 8,192 at
+// 1.0 244 against 295.
+constexpr int kMaxRunPieces = 8;  // candidates r = 1 .. 8
+constexpr int kMaxRun = 288;      // most key tiles of a run (a piece alone may be longer),
+constexpr int kWholeLoad = 3;     // unless every run is a whole row tile and a CU's share is this many of the longest
+constexpr float kItemCost = 4.f;
+constexpr float kMergeCost = 0.0065f;  // key tiles per CU that merging one partial costs
 
 struct PlanView {
   int* hdr;   // [0, 8) queue counters, [8] nq, [9] S, [10] cut row tiles, [11] most pieces,
-              // [12] items per queue and layer,
-              // [14] offset of the item descriptors (ints from the plan's start);
+              // [12] pieces (queue positions) per queue and layer,
+              // [13] key tiles of a run, [14] offset of the piece descriptors (ints from the
+              // plan's start), [15] pieces of a run;
               // [16, 24): what the plan was made from and its checksum (kPlanMagic,
               // n_tiles, RT, H_kv, part_cap, desc_off, two checksum words), [24] 1 when
-              // the last planning launch reused the plan, 0 when it made it
+              // the last planning launch reused the plan, 0 when it made it;
+              // [25] items (runs) per queue and layer, [26] offset of their descriptors,
+              // [27, 29) checksum words of [25, 27) and of the run descriptors
   int* nu;    // [n_tiles] key tiles of row tile i (longest first)
   int* nsp;   // [n_tiles] pieces of row tile i
   int* ppre;  // [n_tiles + 1] first partial slot of row tile i (prefix sums of H_kv x pieces over cut row tiles)
@@ -272,22 +302,18 @@ __device__ __forceinline__ int block_reduce(int v, bool is_max, int* red) {
   return r;
 }
 
-// Inclusive prefix sums (kMax: running maxima) of x over the 1024 threads,
+// Inclusive prefix sums (kMax: running maxima) of x >= 0 over the 1024 threads,
 // continuing from *base (shared); returns this thread's inclusive value and
 // advances *base.
 template <bool kMax = false>
 __device__ __forceinline__ int block_scan(int x, int* wsum, int* base) {
   auto op = [](int u, int v) { return kMax ? max(u, v) : u + v; };
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x = op(x, y);
-  }
+  x = (int)wave_scan<kMax>((unsigned)x);
   if (lane == 63) wsum[wave] = x;
   __syncthreads();
-  int off = *base;
-  for (int w = 0; w < wave; ++w) off = op(off, wsum[w]);
+  const unsigned t = lane < wave ? (unsigned)wsum[lane & 15] : 0u;  // (wave < 16)
+  const int off = op(*base, __builtin_amdgcn_readlane((int)wave_scan<kMax>(t), 63));
   __syncthreads();
   if (threadIdx.x == 1023) *base = op(off, x);
   __syncthreads();
@@ -302,45 +328,65 @@ struct PlanArgs {
   int64_t n_sel, n_tiles, T;
   int RT, Hkv, part_cap;
   int pj_cap, desc_cap;  // ints of the piece sections and item descriptors the workspace holds
-  int desc_off;  // where the item descriptors start
+  int desc_off;  // where the piece descriptors start
+  int run_off;   // where the run descriptors start (as many ints)
+  int grid;      // workgroups of the attention launch
   int* plan;
 };
-// Two checksum words over the plan's ints that the attention and combine
-// kernels read (header [8, 16), pieces and partial slots per row tile, piece
-// sections, item descriptors), each int weighted by its position: unsigned
-// sums, so the order of the terms does not matter.
-__device__ __forceinline__ uint2 plan_checksum(const int* plan, int64_t n_tiles, int nj, int desc_off, int per_q,
-                                               unsigned* red) {
-  unsigned c1 = 0, c2 = 0;
-  auto add = [&](int64_t b, int64_t e) {
-    for (int64_t i = b + threadIdx.x; i < e; i += 1024) {
-      const unsigned v = (unsigned)plan[i], x = (unsigned)i;
-      c1 += v * (2u * x + 1u);
-      c2 += (v ^ (x * 0x9E3779B9u)) * 0x85EBCA6Bu + x;
-    }
-  };
-  const PlanView pv = plan_view(const_cast<int*>(plan), n_tiles);
-  add(8, 16);
-  add(pv.nsp - plan, pv.pj - plan);  // nsp and ppre
-  add(pv.pj - plan, pv.pj - plan + nj + 1);
-  add(desc_off, desc_off + 4 * (int64_t)per_q);
+// The workgroups of the attention launch take their first item without a
+// claim: workgroup b, the rank_in_queue(b)-th of its queue, takes position
+// rank_in_queue(b), and the queue's claim counter starts behind them.
+__host__ __device__ inline int rank_in_queue(int b, int nq) { return b / kXcds * (kXcds / nq) + b % kXcds / nq; }
+__host__ __device__ inline int queue_workgroups(int j, int grid, int nq) {
+  int c = grid / kXcds * (kXcds / nq);
+  for (int x = j; x < grid % kXcds; x += nq) ++c;
+  return c;
+}
+// Two pairs of checksum words over the plan's ints that the attention and
+// combine kernels read, each int weighted by its position: unsigned sums, so
+// the order of the terms does not matter.  Pair 1: header [8, 16), pieces and
+// partial slots per row tile, piece sections, piece descriptors.  Pair 2: header
+// [25, 27) and, where runs have several pieces, their descriptors.  The ints
+// are numbered through, so that a thread's loads are independent of each other.
+struct PlanRegion {
+  int nt, nj, desc_off, per_q, run_off, n_runs;  // (n_runs: run descriptors apart from the piece descriptors)
+  __device__ __forceinline__ int first() const { return 8 + (2 * nt + 1 + nj + 1) + 4 * per_q; }  // ints of pair 1
+  __device__ __forceinline__ int total() const { return first() + 2 + 4 * n_runs; }
+  __device__ __forceinline__ int at(int i) const {  // plan index of the i-th int
+    if (i < 8) return 8 + i;
+    i -= 8;
+    const int rows = 2 * nt + 1 + nj + 1;
+    if (i < rows) return kPlanHdr + nt + i;  // nsp, ppre and pj lie one after the other
+    i -= rows;
+    if (i < 4 * per_q) return desc_off + i;
+    i -= 4 * per_q;
+    return i < 2 ? 25 + i : run_off + i - 2;
+  }
+};
+__device__ __forceinline__ void plan_term(unsigned v, int index, bool second, unsigned (&c)[5]) {
+  const unsigned x = (unsigned)index;
+  const unsigned t1 = v * (2u * x + 1u), t2 = (v ^ (x * 0x9E3779B9u)) * 0x85EBCA6Bu + x;
+  c[0] += second ? 0u : t1;
+  c[1] += second ? 0u : t2;
+  c[2] += second ? t1 : 0u;
+  c[3] += second ? t2 : 0u;
+}
+// Sums of five words over the 1024 threads (every thread gets them).
+__device__ __forceinline__ void block_sum5(unsigned (&c)[5], unsigned* red) {
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    c1 += (unsigned)__shfl_xor((int)c1, o);
-    c2 += (unsigned)__shfl_xor((int)c2, o);
-  }
+  for (int k = 0; k < 5; ++k) c[k] = wave_scan(c[k]);
   __syncthreads();  // red may still be read by an earlier reduction
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6] = c1;
-    red[16 + (threadIdx.x >> 6)] = c2;
-  }
+  if ((threadIdx.x & 63) == 63)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) red[16 * k + (threadIdx.x >> 6)] = c[k];
   __syncthreads();
-  uint2 r = make_uint2(0u, 0u);
-  for (int w = 0; w < 16; ++w) {
-    r.x += red[w];
-    r.y += red[16 + w];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    unsigned r = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) r += red[16 * k + w];
+    c[k] = r;
   }
-  return r;
 }
 
 __device__ void plan_body(const PlanArgs& p) {
@@ -349,7 +395,7 @@ __device__ void plan_body(const PlanArgs& p) {
   const int RT = p.RT, Hkv = p.Hkv, part_cap = p.part_cap, desc_off = p.desc_off;
   int* __restrict__ plan = p.plan;
   __shared__ int red[16];
-  __shared__ unsigned red_u[32];
+  __shared__ unsigned red_u[80];
   __shared__ int wsum[16];
   __shared__ int s_base;
   // the arrays the plan reads back live in LDS when they fit (global memory
@@ -373,13 +419,34 @@ __device__ void plan_body(const PlanArgs& p) {
   // was made from the same counts and sizes and its checksum holds, it is
   // kept and only its claim counters are cleared.  The counts are kept in the
   // plan for that comparison.
+  //
+  // That comparison is what a layer call's planning launch consists of, so its
+  // loads are issued together: the header and the stored counts at once, then
+  // the first ints of every thread's share of the checksum beside the
+  // selection's scan, and one reduction ends both (8,192 tokens: 5.1 us a launch;
+  // with dependent rounds of loads and a reduction for each it took 5.9, and 7.3
+  // with the runs' checksum).
+  constexpr int kEarly = 6;  // checksum ints per thread loaded ahead
+  const int* const hdr = pv.hdr;  // (every thread reads the same values: the decision is uniform)
+  const int nj_s = hdr[11], per_q_s = hdr[12], n_runs_s = hdr[25], ro_s = hdr[26];
+  const int sum_s[4] = {hdr[22], hdr[23], hdr[27], hdr[28]};
+  bool same = hdr[16] == kPlanMagic && hdr[17] == n_tiles && hdr[18] == RT && hdr[19] == Hkv &&
+              hdr[20] == part_cap && hdr[21] == desc_off && nj_s >= 0 && nj_s < p.pj_cap && per_q_s >= 0 &&
+              4 * (int64_t)per_q_s <= p.desc_cap && n_runs_s >= 0 && 4 * (int64_t)n_runs_s <= p.desc_cap &&
+              (ro_s == desc_off || ro_s == p.run_off);
+  const PlanRegion stored = {(int)n_tiles, nj_s, desc_off, per_q_s, ro_s, ro_s == desc_off ? 0 : n_runs_s};
+  const int n_sum = same ? stored.total() : 0;
+  unsigned early[kEarly];
+#pragma unroll
+  for (int k = 0; k < kEarly; ++k) early[k] = tid + 1024 * k < n_sum ? (unsigned)plan[stored.at(tid + 1024 * k)] : 0u;
   int sum = 0, diff = 0;
   if (tid == 0) s_base = 0;
   __syncthreads();
   for (int64_t b = 0; b < n_tiles; b += 1024) {
     const int64_t t = b + tid;
-    int v = 1;
+    int v = 1, old = 0;
     if (t < n_tiles) {
+      old = pv.nu[n_tiles - 1 - t];  // the stored count
       const int64_t ml = min((t + 1) * RT, n_sel) - 1;
       const int64_t g = min((int64_t)sel[ml], T - 1);
       v = g < 0 ? 1 : (int)((g + kKT) / kKT);
@@ -387,33 +454,33 @@ __device__ void plan_body(const PlanArgs& p) {
     v = block_scan<true>(v, wsum, &s_base);
     if (t < n_tiles) {
       const int64_t i = n_tiles - 1 - t;
-      diff |= pv.nu[i] != v;  // (the stored count, read before it is replaced)
+      diff |= old != v;
       pv.nu[i] = v;
       if (in_lds) l_nu[i] = v;
       sum += v;
     }
   }
+  const int nq = n_queues(Hkv), kvq = Hkv / nq;
+  auto start_at = [&](int j) { return j < nq ? queue_workgroups(j, p.grid, nq) : 0; };
   const int nmax = s_base;  // (block_scan ends on a barrier)
-  const int W1 = block_reduce(sum, false, red);
-  {
-    const int* hdr = pv.hdr;  // (every thread reads the same values: the decision is uniform)
-    bool same = block_reduce(diff, true, red) == 0 && hdr[16] == kPlanMagic && hdr[17] == n_tiles &&
-                hdr[18] == RT && hdr[19] == Hkv && hdr[20] == part_cap && hdr[21] == desc_off;
-    if (same) {
-      const int nj_s = hdr[11], per_q_s = hdr[12];
-      same = nj_s >= 0 && nj_s < p.pj_cap && per_q_s >= 0 && 4 * (int64_t)per_q_s <= p.desc_cap;
-      if (same) {
-        const uint2 c = plan_checksum(plan, n_tiles, nj_s, desc_off, per_q_s, red_u);
-        same = c.x == (unsigned)hdr[22] && c.y == (unsigned)hdr[23];
-      }
+  if (same) {  // (uniform)
+    unsigned c[5] = {0u, 0u, 0u, 0u, (unsigned)diff};
+#pragma unroll
+    for (int k = 0; k < kEarly; ++k) {
+      const int i = tid + 1024 * k;
+      if (i < n_sum) plan_term(early[k], stored.at(i), i >= stored.first(), c);
     }
-    if (same) {
-      __syncthreads();  // every thread has read the header
-      if (tid < kXcds) pv.hdr[tid] = 0;  // the queues' claim counters
+    for (int i = tid + 1024 * kEarly; i < n_sum; i += 1024) plan_term((unsigned)plan[stored.at(i)], stored.at(i), i >= stored.first(), c);
+    block_sum5(c, red_u);
+    same = c[4] == 0u && c[0] == (unsigned)sum_s[0] && c[1] == (unsigned)sum_s[1] && c[2] == (unsigned)sum_s[2] &&
+           c[3] == (unsigned)sum_s[3];
+    if (same) {  // (every thread has read the header)
+      if (tid < kXcds) pv.hdr[tid] = start_at(tid);  // the queues' claim counters
       if (tid == 0) pv.hdr[24] = 1;
       return;
     }
   }
+  const int W1 = block_reduce(sum, false, red);
   // piece size: about kItemsPerCU items per CU, raised until the partial
   // slots fit in part_cap (no cut at all always fits)
   const int64_t per = (int64_t)kPlanCUs * kItemsPerCU;
@@ -471,7 +538,6 @@ __device__ void plan_body(const PlanArgs& p) {
     for (int j = max(a_next, 1); j < a; ++j) l_cnt[j] = (int)(i + 1);
   }
   // queue positions of piece j: pj[j] = (cnt_0 + ... + cnt_{j-1}) x KV heads per queue
-  const int nq = n_queues(Hkv), kvq = Hkv / nq;
   if (tid == 0) s_base = 0;
   __syncthreads();
   for (int b = 0; b < nj; b += 1024) {
@@ -480,17 +546,60 @@ __device__ void plan_body(const PlanArgs& p) {
     if (j < nj) pv.pj[j + 1] = l_pj[j + 1] = inc;
   }
   const int n_cut = nj > 1 ? l_cnt[1] : 0;  // (read before l_desc takes descriptors)
+  // Pieces per run: wavefront w estimates the launch with r = w + 1.  With F
+  // items of a whole run (rs key tiles) and R shorter ones, the F take `rounds`
+  // = ceil(F / CUs) turns; what the R need beyond the CUs those leave free
+  // (the remainders taken as evenly spread) takes two more; no launch beats the
+  // mean load.
+  __shared__ float l_est[kMaxRunPieces];
+  const int r_top = in_lds ? min(np_max, kMaxRunPieces) : 1;
+  {
+    const int w = tid >> 6, r = w + 1, rs = min(r * S, nmax);
+    if (r <= r_top) {  // (uniform per wavefront)
+      int full = 0, items = 0, whole = 0, sum_v = 0;
+      const bool may = r == 1 || rs <= kMaxRun || (rs == nmax && (int64_t)W1 * Hkv >= (int64_t)kWholeLoad * nmax * kPlanCUs);
+      if (may)
+        for (int i = tid & 63; i < (int)n_tiles; i += 64) {
+          const int v = nu[i], f = v / rs;
+          full += f;
+          items += f + (f * rs < v);
+          whole += v <= rs;
+          sum_v += v;
+        }
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) {
+        full += __shfl_xor(full, o);
+        items += __shfl_xor(items, o);
+        whole += __shfl_xor(whole, o);
+        sum_v += __shfl_xor(sum_v, o);
+      }
+      const float F = (float)full * Hkv, N = (float)items * Hkv, R = N - F, len = (float)rs + kItemCost;
+      const float rounds = ceilf(F / kPlanCUs), room = rounds * kPlanCUs - F;
+      float t = fmaxf(F > 0.f ? rounds * len : (float)nmax + kItemCost,
+                      1.03f * ((float)sum_v * Hkv + kItemCost * N) / kPlanCUs);
+      if (R > room) t = fmaxf(t, fmaxf(rounds - 1.f, 0.f) * len + 2.f * ((float)rs * (1.f - room / R) + kItemCost));
+      t += kMergeCost * (float)(items - whole) * Hkv;
+      if ((tid & 63) == 0) l_est[w] = may ? t : INFINITY;
+    }
+  }
+  __syncthreads();
+  int run = 1;
+  for (int r = 2; r <= r_top; ++r)
+    if (l_est[r - 1] < l_est[run - 1]) run = r;
+  const int run_tiles = run * S;
   if (tid == 0) {
     const int per_q = s_base + (int)(n_tiles - n_cut) * kvq;
     pv.ppre[0] = 0;
     pv.pj[0] = l_pj[0] = 0;
-    for (int k = 0; k < kXcds; ++k) pv.hdr[k] = 0;  // the queues' claim counters
+    for (int k = 0; k < kXcds; ++k) pv.hdr[k] = start_at(k);  // the queues' claim counters
     pv.hdr[8] = nq;
     pv.hdr[9] = S;
     pv.hdr[10] = n_cut;
     pv.hdr[11] = nj;
     pv.hdr[12] = per_q;
+    pv.hdr[13] = run_tiles;
     pv.hdr[14] = desc_off;
+    pv.hdr[15] = run;
   }
   // Item descriptors, one per queue position (the same in every queue and
   // layer): {row tile, KV head in the queue | piece << 16, first and last key
@@ -531,13 +640,12 @@ __device__ void plan_body(const PlanArgs& p) {
       put(pos, make_int4(i, kvl, 0, nu[i]));
     }
   }
-  if (sort_tail) {  // (uniform)
-    // counting sort of the tail by length (at most S key tiles), longest
-    // first, in 256 buckets
+  // counting sort of nt descriptors in l_desc by length (at most `most` key
+  // tiles), longest first, in 256 buckets, into out[0 .. nt)
+  auto sort_into = [&](int4* out, int nt, int most) {
     __syncthreads();
-    const int nt = per_q_all - r0;
     int shift = 0;
-    while ((S >> shift) > 255) ++shift;
+    while ((most >> shift) > 255) ++shift;
     auto bucket = [&](int4 d) { return 255 - min((d.w - d.z) >> shift, 255); };
     for (int t = tid; t < nt; t += 1024) atomicAdd(&l_bkt[bucket(l_desc[t])], 1);
     __syncthreads();
@@ -551,22 +659,63 @@ __device__ void plan_body(const PlanArgs& p) {
         const int y = __shfl_up(incl, o);
         if (tid >= o) incl += y;
       }
-      int run = incl - tot;
+      int run_to = incl - tot;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        l_bkt[4 * tid + q] = run;
-        run += c4[q];
+        l_bkt[4 * tid + q] = run_to;
+        run_to += c4[q];
       }
     }
     __syncthreads();
     for (int t = tid; t < nt; t += 1024) {
       const int4 d = l_desc[t];
-      desc[r0 + atomicAdd(&l_bkt[bucket(d)], 1)] = d;
+      out[atomicAdd(&l_bkt[bucket(d)], 1)] = d;
     }
+  };
+  if (sort_tail) sort_into(desc + r0, per_q_all - r0, S);  // (uniform)
+  // Run descriptors (of pieces 0, r, 2r, ... of every row tile, in queue order)
+  // when runs have several pieces; else the items are the pieces.  About one
+  // item per CU: all of them longest first; more: the last quarter.
+  int n_runs = per_q_all;
+  if (run > 1) {
+    __syncthreads();  // the piece descriptors are written
+    if (tid == 0) s_base = 0;
+    if (tid < 256) l_bkt[tid] = 0;
+    int loc = 0;
+    for (int i = tid; i < (int)n_tiles; i += 1024) loc += (nsp[i] + run - 1) / run * kvq;
+    n_runs = block_reduce(loc, false, red);
+    const int l0 = n_runs * nq <= 2 * kPlanCUs ? 0 : n_runs - (n_runs + 3) / 4;
+    const bool sorted = n_runs - l0 <= kPlanSortCap;
+    int4* const out = (int4*)(plan + p.run_off);
+    for (int b = 0; b < per_q_all; b += 1024) {
+      const int pos = b + tid;
+      int4 d = make_int4(0, 0, 0, 0);
+      bool lead = false;
+      if (pos < per_q_all) {
+        d = desc[pos];
+        lead = (d.y >> 16) % run == 0;
+        d.w = min(d.z + run_tiles, nu[d.x]);
+      }
+      const int at = block_scan(lead ? 1 : 0, wsum, &s_base) - 1;
+      if (lead) {
+        if (sorted && at >= l0) l_desc[at - l0] = d;
+        else out[at] = d;
+      }
+    }
+    if (sorted) sort_into(out + l0, n_runs - l0, run_tiles);
   }
   // what the plan was made from, and its checksum, for the next call to compare
   __syncthreads();  // every part of the plan is written
-  const uint2 c = plan_checksum(plan, n_tiles, nj, desc_off, per_q_all, red_u);
+  const int ro = run > 1 ? p.run_off : desc_off;
+  if (tid == 0) {
+    pv.hdr[25] = n_runs;
+    pv.hdr[26] = ro;
+  }
+  __syncthreads();
+  const PlanRegion made = {(int)n_tiles, nj, desc_off, per_q_all, ro, run > 1 ? n_runs : 0};
+  unsigned c[5] = {0u, 0u, 0u, 0u, 0u};
+  for (int i = tid; i < made.total(); i += 1024) plan_term((unsigned)plan[made.at(i)], made.at(i), i >= made.first(), c);
+  block_sum5(c, red_u);
   if (tid == 0) {
     pv.hdr[16] = kPlanMagic;
     pv.hdr[17] = (int)n_tiles;
@@ -574,9 +723,11 @@ __device__ void plan_body(const PlanArgs& p) {
     pv.hdr[19] = Hkv;
     pv.hdr[20] = part_cap;
     pv.hdr[21] = desc_off;
-    pv.hdr[22] = (int)c.x;
-    pv.hdr[23] = (int)c.y;
+    pv.hdr[22] = (int)c[0];
+    pv.hdr[23] = (int)c[1];
     pv.hdr[24] = 0;
+    pv.hdr[27] = (int)c[2];
+    pv.hdr[28] = (int)c[3];
   }
 }
 
@@ -740,16 +891,18 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   };
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int jq;  // this workgroup's queue: workgroup b runs on XCD b mod 8, and the XCDs x = j (mod nq) share queue j
+  int first;  // and its first item, taken without a claim
   {
     const PlanView pv = plan_view(a.plan, a.n_tiles);
     jq = (blockIdx.x % kXcds) % pv.hdr[8];
+    first = rank_in_queue(blockIdx.x, pv.hdr[8]);
   }
   // A claim: the queue position got from this workgroup's queue, or, past
   // its end, the next queue's first free position (whole workgroup; thread 0
   // claims).  -1 when every queue is empty.
   auto claim_rest = [&](const AttnArgs& A, int got) -> int {
     const PlanView pv = plan_view(A.plan, A.n_tiles);
-    const int nq = pv.hdr[8], total_q = pv.hdr[12] * A.layers;
+    const int nq = pv.hdr[8], total_q = pv.hdr[25] * A.layers;
     if (tid == 0) {
       int j = jq;
       for (int t = 1; got >= total_q && t < nq; ++t) {
@@ -814,9 +967,9 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   // planning kernel wrote).
   auto start_item = [&](const AttnArgs& A, int item) -> bool {
     const PlanView pv = plan_view(A.plan, A.n_tiles);
-    const int per_q = pv.hdr[12], nq = pv.hdr[8];
+    const int per_q = pv.hdr[25], nq = pv.hdr[8];
     const int lrel = item / per_q;
-    const int4 dsc = *(const int4*)(A.plan + A.desc_off + 4 * (item - lrel * per_q));
+    const int4 dsc = *(const int4*)(A.plan + pv.hdr[26] + 4 * (item - lrel * per_q));
     const int oi = dsc.x, kv = (dsc.y & 0xffff) * nq + jq;
     if (oi < 0 || oi >= A.n_tiles || kv >= A.Hkv || dsc.z < 0 || dsc.w < dsc.z) return false;
     const int key_begin = (int)min((int64_t)dsc.z * kKT, A.T);
@@ -863,7 +1016,7 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   const float sc = a.scale_log2;
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 
-  if (!begin_next(a, tid == 0 ? atomicAdd(&plan_view(a.plan, a.n_tiles).hdr[jq], 1) : 0)) return;  // every queue is empty
+  if (!begin_next(a, first)) return;  // every queue is empty
   __syncthreads();  // s_it is written
   int got = 0;      // thread 0: the next claim, made during the item's last key tiles
 
@@ -949,7 +1102,7 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
     };
 
     // Causal mask and running max of the tile starting at key kt; rescales the
-    // accumulators when the max grew by more than 2^8.
+    // accumulators when the max grew by more than 2^5.
     auto mask_max = [&](int kt, f32x16& s0, f32x16& s1) {
       // accumulator register r of block b holds key kt + 32b + 8(r/4) + 4hi + r%4
       if (kt + kKT - 1 > g_wmin) {
@@ -1101,6 +1254,7 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
     const bool more = begin_next(A, got);
     const int layer = A.lb + lrel;
     const int nsp = pv.nsp[oi];
+    const bool whole = nsp <= pv.hdr[15];     // the run covers the row tile: no partial
     const int piece = min(piece_f, nsp - 1);  // (a bound, as in start_item)
     const int64_t m0 = (A.n_tiles - 1 - oi) * RT;
     const bool valid = g_q >= 0;
@@ -1119,7 +1273,7 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
     };
     auto get = [&](int row, int c) -> u32x4 { return *(const u32x4*)(tb + row * kRow + ((c ^ (row & 15)) << 4)); };
     // accumulator register r of d-block b holds dim 32b + 8(r/4) + 4hi + r%4
-    if (nsp == 1) {
+    if (whole) {
       const float inv = valid ? 1.f / l_tot : 0.f;
 #pragma unroll
       for (int d = 0; d < 4; ++d)
@@ -1194,8 +1348,8 @@ __global__ __launch_bounds__(256) void sel_attn_combine(const AttnArgs a) {
   const int w = blockIdx.x % kWaves;
   const int kvh = (blockIdx.x / kWaves) % a.Hkv;
   const int64_t oi = blockIdx.x / (kWaves * a.Hkv);  // longest-first order
-  const int nsp = pv.nsp[oi];
-  if (nsp == 1) return;  // not cut: written directly
+  const int nsp = pv.nsp[oi], run = pv.hdr[15];
+  if (nsp <= run) return;  // one run: written directly
   const int layer = a.lb + blockIdx.y;
   const int64_t slot0 = (int64_t)blockIdx.y * a.part_cap + pv.ppre[oi] + kvh * nsp;
   const int64_t m0 = (a.n_tiles - 1 - oi) * RT;
@@ -1208,20 +1362,21 @@ __global__ __launch_bounds__(256) void sel_attn_combine(const AttnArgs a) {
   const int h = kvh * G + qv % G;
   const float* ml0 = a.part_ml + (slot0 * kQPerWG + qv) * 4;
   const uint16_t* po0 = a.part + (slot0 * kQPerWG + qv) * 128 + 16 * d16;
-  constexpr int64_t kSlotMl = kQPerWG * 4, kSlotPo = kQPerWG * 128;  // one partial slot apart
+  const int np = (nsp + run - 1) / run;  // partials: one per run, in its first piece's slot
+  const int64_t slot_ml = (int64_t)run * kQPerWG * 4, slot_po = (int64_t)run * kQPerWG * 128;
   float M = -INFINITY;
 #pragma unroll 8
-  for (int p = 0; p < nsp; ++p) M = fmaxf(M, ml0[p * kSlotMl]);
+  for (int p = 0; p < np; ++p) M = fmaxf(M, ml0[p * slot_ml]);
   float Lsum = 0.f;
   f32x4 acc[4] = {};
   // piece order, several pieces' loads in flight
 #pragma unroll 4
-  for (int p = 0; p < nsp; ++p) {
-    const f32x4 ml = *(const f32x4*)(ml0 + p * kSlotMl);
+  for (int p = 0; p < np; ++p) {
+    const f32x4 ml = *(const f32x4*)(ml0 + p * slot_ml);
     const float wgt = ml[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[0] - M) * ml[1];
     Lsum += wgt;
     const float sw = wgt * __builtin_ldexpf(1.f, (int)ml[2]);
-    const uint16_t* pp = po0 + p * kSlotPo;
+    const uint16_t* pp = po0 + p * slot_po;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const f16x4 po = *(const f16x4*)(pp + 4 * k);
@@ -1289,7 +1444,8 @@ AttnPlan plan_attention(const Geo& g, int64_t n_sel, int layers_per_call, int64_
   // item descriptors (4 ints each) after the plan's arrays, one per queue position
   const int64_t per_q_bound = plan_per_q_bound(p.n_tiles, g.Hkv, p.part_cap);
   p.desc_off = (int)((plan_ints(p.n_tiles, max_pieces) + 3) / 4 * 4);
-  p.ws_fixed_bytes = ((p.desc_off + 4 * per_q_bound) * sizeof(int) + 255) / 256 * 256;
+  // (piece descriptors, then as many run descriptors)
+  p.ws_fixed_bytes = ((p.desc_off + 8 * per_q_bound) * sizeof(int) + 255) / 256 * 256;
   p.ws_bytes_per_layer = (size_t)p.part_cap * kQPerWG * (128 * sizeof(uint16_t) + 4 * sizeof(float));
   return p;
 }
@@ -1331,6 +1487,8 @@ static void launch_mfma_g(const AttnArgs& a, const Rows& rows, const ScatterArgs
   pa.desc_off = a.desc_off;
   pa.pj_cap = (int)plan_max_pieces(a.T) + 1;
   pa.desc_cap = (int)(4 * plan_per_q_bound(a.n_tiles, a.Hkv, a.part_cap));
+  pa.run_off = a.desc_off + pa.desc_cap;
+  pa.grid = (int)mfma_grid(a);
   pa.plan = a.plan;
   if (ra) {
     TraceScope tr("plan_rope_scatter", s);

@@ -78,6 +78,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 __device__ __forceinline__ uint16_t f32_to_bf16(float x) { return (uint16_t)(pack_bf16x2(x, 0.f) & 0xffffu); }
 
+// Inclusive prefix sums over the wavefront (kMax: running maxima of values >= 0)
+// in six DPP steps; every lane must be active.
+template <bool kMax = false>
+__device__ __forceinline__ unsigned wave_scan(unsigned x) {
+  auto op = [](unsigned u, int v) { return kMax ? max(u, (unsigned)v) : u + (unsigned)v; };
+  x = op(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));  // row_shr 1, 2, 4, 8
+  x = op(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));  // lane 15 to rows 1 and 3
+  x = op(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));  // lane 31 to rows 2 and 3
+  return x;
+}
+
 // ------------------------------------------------------------------ rotation (Eq. 2, Eq. 3)
 // cos/sin of a rotary angle formed in float64: reduced modulo 2*pi, evaluated
 // in float64 and rounded once to float32.

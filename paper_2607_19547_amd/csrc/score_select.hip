@@ -129,17 +129,6 @@ __global__ __launch_bounds__(kRankMax) void rank_select_topk(const float* __rest
   if (take && pos < k) sel[pos] = cs1 + tid;
 }
 
-// Inclusive prefix sum over the wavefront (six DPP adds; every lane active).
-__device__ __forceinline__ unsigned wave_scan(unsigned x) {
-  x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
-  x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
-  x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
-  x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
-  x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // lane 15 to rows 1 and 3
-  x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // lane 31 to rows 2 and 3
-  return x;
-}
-
 // A histogram of kBins bins in kCopies copies: bin d's copies start at word
 // hist_at(d).  Thread t of a scan reads `per` bins side by side; two words of
 // padding after every eight spread those reads over the banks.

@@ -1,0 +1,89 @@
+"""Runs of key pieces (the attention launch's items): the run descriptors in the
+plan take every r-th piece of each row tile and cover its key tiles once, short
+runs come last, and the outputs (one partial per run, none where a run is a whole
+row tile) match float64 attention; fresh, kept and batched plans give the same
+bits."""
+import math
+
+import numpy as np
+import pytest
+
+from tests.gpu_util import log
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+HDR = 32
+# G, Hkv, T, n_sel, whole: about one item per CU, a few per CU, whole row tiles
+CASES = [(8, 2, 32768, 1536, False), (4, 4, 16384, 1434, False), (1, 8, 12000, 1500, False), (16, 1, 40000, 2100, False),
+         (32, 1, 9000, 1000, False), (8, 8, 3000, 2700, True), (32, 2, 4000, 2500, True)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu(built_lib):
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+
+
+def _reference(q, k, v, sel, h, g):
+    t = sel.long()
+    s = torch.mm(q[h].double(), k[h // g].double().t()) / math.sqrt(128)
+    s.masked_fill_(torch.arange(k.shape[1], device="cuda")[None] > t[:, None], -math.inf)
+    return torch.mm(torch.softmax(s, dim=1), v[h // g].double()), torch.logsumexp(s, dim=1)
+
+
+@pytest.mark.parametrize("G,hkv,T,k,whole", CASES)
+def test_runs_cover_every_piece_and_match(G, hkv, T, k, whole):
+    from paper_2607_19547_amd import binding as b
+    log(f"case runs G={G} Hkv={hkv} T={T} k={k}")
+    cs1, L, hq, D = T // 16, 2, G * hkv, 128
+    n = T - cs1
+    geo = b.Geo(L, hq, hkv, D, (16, 24, 24), "bf16", np.array([0, cs1, T], np.int64))
+    gen = torch.Generator(device="cuda").manual_seed(T + k)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=gen).to(torch.bfloat16)
+    K, V, Q, KF, VF = r(L, hkv, T, D), r(L, hkv, T, D), r(L, hq, n, D), r(L, hkv, n, D), r(L, hkv, n, D)
+    sel = (torch.randperm(n, device="cuda", generator=gen)[:k].sort().values + cs1).to(torch.int32)
+    out = torch.empty((L, hq, k, D), dtype=torch.bfloat16, device="cuda")
+    lse = torch.empty((L, hq, k), dtype=torch.float32, device="cuda")
+    ws = torch.zeros(b.selective_attend_scatter_workspace(geo, k, L), dtype=torch.uint8, device="cuda")
+    b.selective_attend_scatter(geo, K, V, 0, 1, sel, k, Q, KF, VF, out, lse, ws)
+    torch.cuda.synchronize()
+    plan = ws.view(torch.int32).cpu().numpy()
+    hdr = plan[:HDR]
+    S, per_q, rs, off, run, n_runs, ro = (int(hdr[i]) for i in (9, 12, 13, 14, 15, 25, 26))
+    nt = int(hdr[17])
+    nu, nsp = plan[HDR:HDR + nt], plan[HDR + nt:HDR + 2 * nt]
+    assert run >= 2 and rs == run * S, "the case is one with runs of several pieces"
+    assert (rs >= nu[0]) == whole
+    pieces = plan[off:off + 4 * per_q].reshape(per_q, 4)
+    runs = plan[ro:ro + 4 * n_runs].reshape(n_runs, 4)
+    lead = sorted((int(i), int(y), int(z), int(min(z + rs, nu[i]))) for i, y, z, _ in pieces if (int(y) >> 16) % run == 0)
+    assert sorted(tuple(map(int, x)) for x in runs) == lead and ro != off
+    kvq = hkv // int(hdr[8])
+    assert n_runs == sum(-(-int(p) // run) for p in nsp) * kvq
+    covered = {}
+    for i, y, z, e in lead:
+        covered.setdefault((i, y & 0xffff), []).append((z, e))
+    for (i, _), spans in covered.items():
+        spans.sort()
+        assert spans[0][0] == 0 and spans[-1][1] == nu[i] and all(x[1] == y[0] for x, y in zip(spans, spans[1:]))
+    lens = [int(e - z) for _, _, z, e in runs]
+    tail = lens if n_runs * int(hdr[8]) <= 512 else lens[n_runs - (n_runs + 3) // 4:]
+    shift = 0
+    while (rs >> shift) > 255:
+        shift += 1
+    assert all(min(x >> shift, 255) >= min(y >> shift, 255) for x, y in zip(tail, tail[1:])), "longest first"
+    # the second layer keeps the plan; a batched call over both layers on a fresh workspace gives the same bits
+    b.selective_attend_scatter(geo, K, V, 1, 2, sel, k, Q, KF, VF, out, lse, ws)
+    out2, lse2 = torch.empty_like(out), torch.empty_like(lse)
+    b.selective_attend_scatter(geo, K, V, 0, L, sel, k, Q, KF, VF, out2, lse2, torch.zeros_like(ws))
+    torch.cuda.synchronize()
+    assert int(ws.view(torch.int32)[24]) == 1 and torch.equal(out, out2) and torch.equal(lse, lse2)
+    rows = sel.long() - cs1
+    for layer, h in ((0, 0), (1, hq - 1)):
+        o, l = _reference(Q[layer][:, rows], K[layer], V[layer], sel, h, G)
+        err = float((out[layer, h].double() - o).norm() / o.norm())
+        lerr = float((lse[layer, h].double() - l).abs().max())
+        log(f"  run {run} x {S} tiles, {n_runs} items per queue: layer {layer} head {h} rel-L2 {err:.2e}, lse {lerr:.2e}")
+        # bf16 probabilities and one bf16 rounding of the result: 2^-9 each at most, in the mean square below 3e-3
+        assert err <= 5e-3 and lerr <= 1e-2
