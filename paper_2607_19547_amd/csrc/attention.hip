@@ -143,7 +143,10 @@ struct AttnArgs {
   int cs1, Hq, Hkv, lb, layers;
   int part_cap;      // partial slots per layer
   int q_by_slot;     // q is [layers in call][H_q][n_sel][128] (rows in selection order), else [L][H_q][n][128]
-  int desc_off;      // piece descriptors in the plan (set by the planning kernel's caller)
+  int desc_off;      // piece descriptors in the plan
+  int run_off;       // run descriptors in the plan
+  int desc_cap;      // ints that each of the two has room for
+  int grid;          // workgroups of the attention launch
   const float2* rope_tab;  // [n_sel][64] cos/sin of the selected tokens: q holds pre-rotary queries, rotated on
                            // load; NULL: q is already rotated
   float scale_log2;  // log2(e) / sqrt(D)
@@ -283,7 +286,7 @@ inline size_t plan_ints(int64_t n_tiles, int64_t max_pieces) {
 }
 // Queues: one per KV head (shared by 8/H_kv XCDs), one per XCD, or one.
 __host__ __device__ inline int n_queues(int Hkv) {
-  return Hkv % kXcds == 0 ? kXcds : (kXcds % Hkv == 0 ? Hkv : 1);
+  return Hkv % kXcds == 0 ? kXcds : (Hkv == 1 || Hkv == 2 || Hkv == 4 ? Hkv : 1);
 }
 
 // Sum or max over the 1024 threads of the planning workgroup (every thread
@@ -875,7 +878,7 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   // from a lane index read afresh (an opaque value the compiler cannot hoist
   // out of the item loop).
   __shared__ int s_claim[2];
-  __shared__ int s_it[8];  // the current item: layer in call, row tile, KV head, piece, first and end key
+  __shared__ int s_it[8];  // the current item: layer in call, row tile, KV head, piece, first and end key; [6]: items are left to claim
   typedef const __attribute__((address_space(4))) AttnArgs* ArgPtr;  // the argument segment (scalar loads)
   const ArgPtr argp = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
   auto args = [&]() -> AttnArgs {  // the arguments, read anew where they are used
@@ -891,12 +894,6 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   };
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int jq;  // this workgroup's queue: workgroup b runs on XCD b mod 8, and the XCDs x = j (mod nq) share queue j
-  int first;  // and its first item, taken without a claim
-  {
-    const PlanView pv = plan_view(a.plan, a.n_tiles);
-    jq = (blockIdx.x % kXcds) % pv.hdr[8];
-    first = rank_in_queue(blockIdx.x, pv.hdr[8]);
-  }
   // A claim: the queue position got from this workgroup's queue, or, past
   // its end, the next queue's first free position (whole workgroup; thread 0
   // claims).  -1 when every queue is empty.
@@ -965,11 +962,7 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   // then the buffer ranges of its plane and its key tiles 0 and 1 into ring
   // slots 0 and 1.  False for a damaged plan entry (never for a plan the
   // planning kernel wrote).
-  auto start_item = [&](const AttnArgs& A, int item) -> bool {
-    const PlanView pv = plan_view(A.plan, A.n_tiles);
-    const int per_q = pv.hdr[25], nq = pv.hdr[8];
-    const int lrel = item / per_q;
-    const int4 dsc = *(const int4*)(A.plan + pv.hdr[26] + 4 * (item - lrel * per_q));
+  auto place_item = [&](const AttnArgs& A, int lrel, int nq, int4 dsc) -> bool {
     const int oi = dsc.x, kv = (dsc.y & 0xffff) * nq + jq;
     if (oi < 0 || oi >= A.n_tiles || kv >= A.Hkv || dsc.z < 0 || dsc.w < dsc.z) return false;
     const int key_begin = (int)min((int64_t)dsc.z * kKT, A.T);
@@ -992,10 +985,41 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
     fetch(key_begin + kKT, up_k1, lo_v1);
     return true;
   };
+  auto start_item = [&](const AttnArgs& A, int item) -> bool {
+    const PlanView pv = plan_view(A.plan, A.n_tiles);
+    const int per_q = pv.hdr[25], nq = pv.hdr[8];
+    const int lrel = item / per_q;
+    return place_item(A, lrel, nq, *(const int4*)(A.plan + pv.hdr[26] + 4 * (item - lrel * per_q)));
+  };
   auto begin_next = [&](const AttnArgs& A, int got) {  // claims until an item starts; false when none is left
     int item = claim_rest(A, got);
     while (item >= 0 && !start_item(A, item)) item = claim_one(A);
     return item >= 0;
+  };
+  // The first item, taken without a claim.  Its descriptor is loaded beside the
+  // header, from both places it can be in (a workgroup past its queue's items
+  // reads another's, unused).  Where the first items are all there is, nothing
+  // is claimed later either.  (A layer of the 8,192-token composition, 246 items:
+  // with the header's ints and the descriptor read one after the other an item
+  // started 2.8 us after the launch, and the claims with nothing left to claim,
+  // one atomic per workgroup on each queue, held back its results by 3.2 us on
+  // average and 7.6 at most.  The launch: 41.4 us before, 35.3 now.)
+  auto begin_first = [&]() -> bool {
+    const int nq = n_queues(a.Hkv), first = rank_in_queue(blockIdx.x, nq);
+    jq = (blockIdx.x % kXcds) % nq;
+    const int at = min(4 * first, a.desc_cap - 4);
+    int4 dsc = *(const int4*)(a.plan + a.desc_off + at), d_run = *(const int4*)(a.plan + a.run_off + at);
+    const PlanView pv = plan_view(a.plan, a.n_tiles);
+    int per_q = pv.hdr[25], off = pv.hdr[26];
+    asm volatile("" : "+s"(dsc.x), "+s"(dsc.y), "+s"(dsc.z), "+s"(dsc.w), "+s"(d_run.x), "+s"(d_run.y), "+s"(d_run.z),
+                 "+s"(d_run.w), "+s"(per_q), "+s"(off));  // (loaded together)
+    if (off == a.run_off) dsc = d_run;
+    const int total_q = per_q * a.layers;
+    const bool claims = total_q > a.grid / kXcds * (kXcds / nq) + a.grid % kXcds / nq;  // (the smallest queue's workgroups)
+    if (tid == 0) s_it[6] = claims;
+    if (first < per_q && at == 4 * first && place_item(a, 0, nq, dsc)) return true;
+    if (first >= per_q && first < total_q && start_item(a, first)) return true;
+    return claims && begin_next(a, total_q);
   };
 
   // per-lane LDS offsets of the MFMA operands
@@ -1016,7 +1040,7 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   const float sc = a.scale_log2;
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 
-  if (!begin_next(a, first)) return;  // every queue is empty
+  if (!begin_first()) return;  // every queue is empty
   __syncthreads();  // s_it is written
   int got = 0;      // thread 0: the next claim, made during the item's last key tiles
 
@@ -1249,9 +1273,10 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
     // pass through slots 2 and 3.
     const AttnArgs A = args();
     const PlanView pv = plan_view(A.plan, A.n_tiles);
-    if (n_kt == 0 && tid == 0) got = claim_add(&pv.hdr[jq]);
+    const bool claims = it_field(6);
+    if (n_kt == 0 && tid == 0 && claims) got = claim_add(&pv.hdr[jq]);
     const int lrel = it_field(0), oi = it_field(1), kv = it_field(2), piece_f = it_field(3);
-    const bool more = begin_next(A, got);
+    const bool more = claims && begin_next(A, got);
     const int layer = A.lb + lrel;
     const int nsp = pv.nsp[oi];
     const bool whole = nsp <= pv.hdr[15];     // the run covers the row tile: no partial
@@ -1331,10 +1356,10 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
         *(u32x4*)(pp + R * 128 + 8 * c) = get(R, c);
       }
     }
+    if (!more) break;
     // every wavefront is done with ring slots 2 and 3 before the next item's
     // key tile 2 is fetched there, and s_it holds the next item
     __syncthreads();
-    if (!more) break;
   }
 }
 
@@ -1486,9 +1511,9 @@ static void launch_mfma_g(const AttnArgs& a, const Rows& rows, const ScatterArgs
   pa.part_cap = a.part_cap;
   pa.desc_off = a.desc_off;
   pa.pj_cap = (int)plan_max_pieces(a.T) + 1;
-  pa.desc_cap = (int)(4 * plan_per_q_bound(a.n_tiles, a.Hkv, a.part_cap));
-  pa.run_off = a.desc_off + pa.desc_cap;
-  pa.grid = (int)mfma_grid(a);
+  pa.desc_cap = a.desc_cap;
+  pa.run_off = a.run_off;
+  pa.grid = a.grid;
   pa.plan = a.plan;
   if (ra) {
     TraceScope tr("plan_rope_scatter", s);
@@ -1507,7 +1532,7 @@ static void launch_mfma_g(const AttnArgs& a, const Rows& rows, const ScatterArgs
   }
   {
     TraceScope tr("sel_attn_mfma", s);
-    CS_LAUNCH(tr, (sel_attn_mfma<G, Rows>), dim3((unsigned)mfma_grid(a)), dim3(kThreads), 0, s, a, rows);
+    CS_LAUNCH(tr, (sel_attn_mfma<G, Rows>), dim3((unsigned)a.grid), dim3(kThreads), 0, s, a, rows);
   }
   if (a.part_cap > 0) {
     TraceScope tr("sel_attn_combine", s);
@@ -1585,9 +1610,12 @@ cs_status launch_attention(const Geo& g, const AttnPlan& p, const CacheView& cv,
     a.part_cap = p.part_cap;
     a.q_by_slot = q_by_slot ? 1 : 0;
     a.desc_off = p.desc_off;
+    a.desc_cap = (int)(4 * plan_per_q_bound(p.n_tiles, g.Hkv, p.part_cap));
+    a.run_off = a.desc_off + a.desc_cap;
     a.rope_tab = rope ? (const float2*)rope->tab : nullptr;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.D));
-    cs_status stg = check_grid(mfma_grid(a), 1, 1, kThreads, "selective attention");
+    a.grid = (int)mfma_grid(a);
+    cs_status stg = check_grid(a.grid, 1, 1, kThreads, "selective attention");
     if (!stg && rope) stg = check_grid(1 + (int64_t)ra.nblk * layers, 1, 1, 1024, "rotary scatter");
     if (!stg && a.part_cap > 0) stg = check_grid(combine_grid(a), layers, 1, 256, "partial combine");
     if (stg || check_only) return stg;

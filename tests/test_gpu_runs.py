@@ -87,3 +87,37 @@ def test_runs_cover_every_piece_and_match(G, hkv, T, k, whole):
         log(f"  run {run} x {S} tiles, {n_runs} items per queue: layer {layer} head {h} rel-L2 {err:.2e}, lse {lerr:.2e}")
         # bf16 probabilities and one bf16 rounding of the result: 2^-9 each at most, in the mean square below 3e-3
         assert err <= 5e-3 and lerr <= 1e-2
+
+
+# Row tiles of 32 / G x 8 rows; short caches, so that every item is a whole row
+# tile: just fewer items than the 256 workgroups (nothing is claimed), as many,
+# and just more, with one queue per call, per KV head and per XCD.
+@pytest.mark.parametrize("G,hkv,L,k", [(32, 1, 3, 680), (32, 1, 2, 1021), (32, 1, 3, 681), (32, 3, 1, 680), (32, 3, 1, 681),
+                                       (32, 4, 1, 504), (32, 4, 1, 512), (32, 4, 1, 513), (32, 8, 1, 255), (32, 8, 1, 257),
+                                       (16, 2, 1, 1020), (8, 2, 1, 33), (32, 1, 1, 1)])
+def test_items_around_one_per_workgroup(G, hkv, L, k):
+    from paper_2607_19547_amd import binding as b
+    log(f"case one item each G={G} Hkv={hkv} L={L} k={k}")
+    T, cs1, hq, D = 1024, 2, G * hkv, 128
+    n = T - cs1
+    geo = b.Geo(L, hq, hkv, D, (16, 24, 24), "bf16", np.array([0, cs1, T], np.int64))
+    gen = torch.Generator(device="cuda").manual_seed(G * 1000 + k)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=gen).to(torch.bfloat16)
+    K, V, Q, KF, VF = r(L, hkv, T, D), r(L, hkv, T, D), r(L, hq, n, D), r(L, hkv, n, D), r(L, hkv, n, D)
+    sel = (torch.randperm(n, device="cuda", generator=gen)[:k].sort().values + cs1).to(torch.int32)
+    got = []
+    for per in (1, L):  # a call per layer; one call
+        k2, v2 = K.clone(), V.clone()
+        out = torch.full((L, hq, k, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ws = torch.zeros(b.selective_attend_scatter_workspace(geo, k, per), dtype=torch.uint8, device="cuda")
+        for layer in range(0, L, per):
+            b.selective_attend_scatter(geo, k2, v2, layer, layer + per, sel, k, Q, KF, VF, out, None, ws)
+        got.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1])
+    for layer in range(L):
+        for h in (0, hq - 1):
+            want, _ = _reference(Q[layer][:, sel.long() - cs1], k2[layer], v2[layer], sel, h, G)
+            # bf16 probabilities and outputs: 2^-9 each, relative to the row
+            err = (got[0][layer, h].double() - want).norm() / want.norm()
+            assert err <= 5e-3, (layer, h, float(err))
