@@ -22,7 +22,7 @@
 // the L1 rate, so LDS staging would add barriers and save nothing.
 //
 // Measured (4,096 float32 tokens, 512 selected rows, 16 query heads, 2 KV heads,
-// D = 128, scatter included): 169 us, 76 TFLOP/s, against 2,870 us for one
+// D = 128, scatter included): 167 us, 77 TFLOP/s, against 2,870 us for one
 // wavefront per (row, head) with scalar FMAs, which it replaces at every
 // geometry (bf16 D = 64: 107 against 960 us; D = 512: 772 against 4,288 us; 64
 // tokens of D = 16: 13 against 17 us).  The error against float64 halves (5.6e-7
@@ -172,6 +172,10 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
   __shared__ __attribute__((aligned(16))) float lds[kGenQ * kQW > kWavesMax * kGenQ * kGenBufW ? kGenQ * kQW : kWavesMax * kGenQ * kGenBufW];
   __shared__ float s_m[kWavesMax][kGenQ], s_l[kWavesMax][kGenQ];
   __shared__ int s_tok[kGenQ];
+  // rows of a.q and of the results that the query vectors have (the 64-bit
+  // divisions behind them once per vector; once per element they took 1.3 us of
+  // a 168 us layer and about as much of the 64-token composition)
+  __shared__ int64_t s_qrow[kGenQ], s_orow[kGenQ];
   const int nw = blockDim.x >> 6;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane & 31, hi = lane >> 5;
@@ -188,22 +192,19 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
     const int64_t plane = (int64_t)layer * a.Hkv + kv;
     if (tid < kGenQ) {
       const int64_t m = (x0 + tid) / G;
+      const int h = kv * G + (int)(x0 + tid - m * G);
       int t = -1;
       if (m < a.n_sel) t = a.sel[m];
       s_tok[tid] = t >= a.cs1 && t < a.T ? t : -1;  // out-of-contract index: no output
+      s_qrow[tid] = a.q_by_slot ? ((int64_t)blockIdx.z * a.Hq + h) * a.n_sel + m
+                                : ((int64_t)layer * a.Hq + h) * a.n + (t - a.cs1);
+      s_orow[tid] = ((int64_t)layer * a.Hq + h) * a.n_sel + m;
     }
     __syncthreads();
     for (int i = tid; i < kGenQ * 32 * NB; i += blockDim.x) {
       const int r = i / (32 * NB), d = i - r * (32 * NB);
-      const int t = s_tok[r];
       float v = 0.f;
-      if (t >= 0 && d < D) {
-        const int64_t x = x0 + r, m = x / G;
-        const int h = kv * G + (int)(x - m * G);
-        const int64_t qrow = a.q_by_slot ? ((int64_t)blockIdx.z * a.Hq + h) * a.n_sel + m
-                                         : ((int64_t)layer * a.Hq + h) * a.n + (t - a.cs1);
-        v = gen_value(((const E*)a.q)[qrow * D + d]);
-      }
+      if (s_tok[r] >= 0 && d < D) v = gen_value(((const E*)a.q)[s_qrow[r] * D + d]);
       lds[r * kQW + d] = v;
     }
     __syncthreads();
@@ -391,10 +392,7 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
     for (int w = 0; w < nw; ++w) M = fmaxf(M, s_m[w][q]);
     for (int w = 0; w < nw; ++w) L += s_m[w][q] == -INFINITY ? 0.f : s_l[w][q] * expf(s_m[w][q] - M);
     const float f = (m_run == -INFINITY ? 0.f : expf(m_run - M)) / L;
-    if (wave == 0 && hi == 0 && g_q >= 0 && a.lse) {
-      const int64_t x = x0 + q, m = x / G;
-      a.lse[((int64_t)layer * a.Hq + kv * G + (int)(x - m * G)) * a.n_sel + m] = M + logf(L);
-    }
+    if (wave == 0 && hi == 0 && g_q >= 0 && a.lse) a.lse[s_orow[q]] = M + logf(L);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       if (32 * j < D) {  // (uniform)
@@ -407,9 +405,7 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
           if (d < D && s_tok[r] >= 0) {
             float v = 0.f;
             for (int w = 0; w < nw; ++w) v += lds[(w * kGenQ + r) * kGenBufW + (i & 31)];
-            const int64_t x = x0 + r, m = x / G;
-            const int h = kv * G + (int)(x - m * G);
-            gen_store((E*)a.out + (((int64_t)layer * a.Hq + h) * a.n_sel + m) * D + d, v);
+            gen_store((E*)a.out + s_orow[r] * D + d, v);
           }
         }
         __syncthreads();  // the buffer (and s_tok, s_m) is written again
