@@ -10,7 +10,7 @@
 //   S^T = K Q^T         (v_mfma_f32_32x32x16_bf16, K from LDS, Q in VGPRs)
 // so each lane ends up holding 32 scores of ONE query; the softmax runs on
 // those registers (exp2 with the 1/sqrt(D) and log2(e) factors folded into one
-// FMA, a lazy running max that rescales only when the max grows by > 2^8),
+// FMA, a lazy running max that rescales only when the max grows by > 2^5),
 // and the probabilities are packed to bf16 directly as the B operand of
 //   O^T += V^T P^T      (V^T read from LDS with transposing loads).
 // K/V tiles reach LDS by buffer->LDS DMA into a 4-slot ring: while the

@@ -26,10 +26,10 @@
 // wavefront per (row, head) with scalar FMAs, which it replaces at every
 // geometry (bf16 D = 64: 107 against 960 us; D = 512: 772 against 4,288 us; 64
 // tokens of D = 16: 13 against 17 us).  The error against float64 is 5.6e-7 to
-// 9.8e-7 over eight inputs, against 7.5e-7 to 1.1e-6 (shorter sums).  The longest row tile sets the time when there
-// are about as many workgroups as CUs (there 4,096 keys against 3,072 on
-// average); splitting it further would need a workspace, which these calls do
-// not take.
+// 9.8e-7 over eight inputs, against 7.5e-7 to 1.1e-6 (shorter sums).  The
+// longest row tile sets the time when there are about as many workgroups as CUs
+// (there 4,096 keys against 3,072 on average); splitting it further would need
+// a workspace, which these calls do not take.
 #include <math.h>
 
 #include <algorithm>
