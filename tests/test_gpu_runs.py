@@ -121,3 +121,36 @@ def test_items_around_one_per_workgroup(G, hkv, L, k):
             # bf16 probabilities and outputs: 2^-9 each, relative to the row
             err = (got[0][layer, h].double() - want).norm() / want.norm()
             assert err <= 5e-3, (layer, h, float(err))
+
+
+# More items than workgroups in two, four and eight queues; short caches, so that
+# every item is a whole row tile.
+@pytest.mark.parametrize("G,hkv,L,k", [(32, 8, 1, 400), (32, 8, 3, 777), (16, 4, 2, 1000), (32, 2, 3, 1020)])
+def test_workgroups_claim_only_where_positions_are_left(G, hkv, L, k):
+    """Every position is taken once, and a workgroup that finds its queue empty
+    leaves the other queues' counters alone unless they have positions left: one
+    failed claim per workgroup on its own queue, and as many again for the rare
+    claim that comes second (a claim on every queue would be nq per workgroup)."""
+    from paper_2607_19547_amd import binding as b
+    log(f"case claims G={G} Hkv={hkv} L={L} k={k}")
+    T, cs1, hq, D = 1024, 2, G * hkv, 128
+    n = T - cs1
+    geo = b.Geo(L, hq, hkv, D, (16, 24, 24), "bf16", np.array([0, cs1, T], np.int64))
+    gen = torch.Generator(device="cuda").manual_seed(G * 1000 + k)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=gen).to(torch.bfloat16)
+    K, V, Q, KF, VF = r(L, hkv, T, D), r(L, hkv, T, D), r(L, hq, n, D), r(L, hkv, n, D), r(L, hkv, n, D)
+    sel = (torch.randperm(n, device="cuda", generator=gen)[:k].sort().values + cs1).to(torch.int32)
+    out = torch.full((L, hq, k, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.zeros(b.selective_attend_scatter_workspace(geo, k, L), dtype=torch.uint8, device="cuda")
+    b.selective_attend_scatter(geo, K, V, 0, L, sel, k, Q, KF, VF, out, None, ws)
+    torch.cuda.synchronize()
+    hdr = ws[:4 * HDR].view(torch.int32).tolist()
+    nq, positions = hdr[8], hdr[25] * L
+    assert nq * positions > 256, "the case is one with items left to claim"
+    assert all(positions <= c for c in hdr[:nq])
+    assert sum(hdr[:nq]) <= nq * positions + 2 * 256, hdr[:8]
+    for layer in (0, L - 1):
+        for h in (0, hq - 1):
+            want, _ = _reference(Q[layer][:, sel.long() - cs1], K[layer], V[layer], sel, h, G)
+            err = (out[layer, h].double() - want).norm() / want.norm()
+            assert err <= 5e-3, (layer, h, float(err))  # bf16 probabilities and outputs: 2^-9 each
