@@ -240,22 +240,42 @@ constexpr int kXcds = 8;
 // Runs.  An item of the attention launch is a run of `r` consecutive pieces of
 // one row tile for one KV head: the workgroup carries its running max, sum and
 // output through them and leaves one partial (none at all when the run covers
-// the row tile).  The plan picks r, from the pieces' lengths alone, to end the
-// launch soonest: few long items leave little to merge and few prologues and
-// epilogues (an item's fixed cost is about kItemCost key tiles), but must
-// share out evenly over the CUs.  The estimate (plan_body) follows a model of
-// the launch that reproduces the measured order of the candidates; best about
-// one item per CU for a layer of up to 200 key tiles per CU, two to four beyond
-// that (kMaxRun: longer items leave CUs idle at the end; 65,536 tokens at rho =
-// 0.1: 1,459 us a layer with items of 281 tiles, 1,497 with 138, 1,506 with
-// 908).  Measured for one layer, 16 query heads, against r = 1: 32,768 tokens at
-// rho = 0.05 213-228 us against 259, 16,384 at 0.1 117-128 against 148, 8,192 at
-// 1.0 244 against 295.
-constexpr int kMaxRunPieces = 8;  // candidates r = 1 .. 8
-constexpr int kMaxRun = 288;      // most key tiles of a run (a piece alone may be longer),
-constexpr int kWholeLoad = 3;     // unless every run is a whole row tile and a CU's share is this many of the longest
-constexpr float kItemCost = 4.f;
+// the row tile).  Few long items leave little to merge and few prologues and
+// epilogues (an item's fixed cost is about kItemCost key tiles), but must share
+// out evenly over the CUs.  The plan takes the r = 1 .. 8 whose launch ends
+// soonest by this estimate, from the pieces' lengths alone, in key tiles:
+//  * never before the mean load, an item's fixed cost included;
+//  * two items per workgroup or fewer: all are handed out longest first, so the
+//    i-th longest beyond the first round joins the i-th shortest of it, and the
+//    latest of these pairs ends the launch, or the longest item alone;
+//  * more: whole rounds of full runs first, and then the same for what is left
+//    (where that is two items per workgroup or fewer);
+//  * and with more than two a launch ends some per cent after the mean load, and
+//    not before the longest run of the last quarter, which is handed out longest
+//    first when three quarters of the load are done (kTail).  That run is a full
+//    one, except where each queue is one KV head, the runs are whole row tiles
+//    (the order is longest first throughout) and the head's keys and values fit
+//    an XCD's L2 (beyond that, row tiles that drift apart read them from memory:
+//    65,536 tokens at rho = 0.2, 3.10 ms a layer against 2.95): then it is the
+//    row tile three quarters down the list;
+//  * plus the merge of the partials (kMergeCost).
+// Measured, every r on 1,036 layers (ten head layouts of 8 to 64 query and 1 to
+// 16 KV heads, 1,536 to 131,072 tokens, rho 0.01 to 1), against the kernel
+// without runs: 0.872 of the time in the geometric mean, where r = 1 takes 0.923
+// and the best r of each layer 0.870; 2% longer at most (68,000 tokens, one KV
+// head, rho = 0.2: 1,615 us against 1,588).  With an absolute bound on a run's
+// length instead of the third and fourth term, fitted at 65,536 tokens, up to
+// 10% longer (16,384 tokens, 28 / 7 heads, rho = 0.35).  The estimate adds 1 to
+// 2 us to a launch that plans; one that keeps its plan does not make it.
+// The estimate is that of one layer also where a call takes several, so that
+// calls over any number of layers share a plan and give the same bits.
+constexpr int kMaxRunPieces = 8;       // candidates r = 1 .. 8
+constexpr float kItemCost = 7.f;       // key tiles: 12 us (5 to 8 choose about alike)
+constexpr float kTail = 1.05f;         // over the mean load (1.03 to 1.06 choose about alike)
+constexpr float kTailRun = 0.95f;      // a queue of one KV head: the run starts a little before (0.9 to 0.97)
+constexpr float kRunGain = 0.99f;      // runs of several pieces are taken where they gain this much
 constexpr float kMergeCost = 0.0065f;  // key tiles per CU that merging one partial costs
+constexpr int kL2Tiles = 128;          // key tiles whose keys and values (32 KB) fit an XCD's 4 MB L2
 
 struct PlanView {
   int* hdr;   // [0, 8) queue counters, [8] nq, [9] S, [10] cut row tiles, [11] most pieces,
@@ -549,46 +569,85 @@ __device__ void plan_body(const PlanArgs& p) {
     if (j < nj) pv.pj[j + 1] = l_pj[j + 1] = inc;
   }
   const int n_cut = nj > 1 ? l_cnt[1] : 0;  // (read before l_desc takes descriptors)
-  // Pieces per run: wavefront w estimates the launch with r = w + 1.  With F
-  // items of a whole run (rs key tiles) and R shorter ones, the F take `rounds`
-  // = ceil(F / CUs) turns; what the R need beyond the CUs those leave free
-  // (the remainders taken as evenly spread) takes two more; no launch beats the
-  // mean load.
+  // Pieces per run: wavefront w estimates the launch with r = w + 1 (see
+  // kMaxRunPieces).  A queue's workgroups are g; item lengths are counted in
+  // kRunBkts buckets, beyond the piece counts in l_desc's LDS.
+  constexpr int kRunBkts = 256;
+  static_assert((kMaxPieces + kMaxRunPieces * kRunBkts) * sizeof(int) <= sizeof(l_desc), "the counts fit");
   __shared__ float l_est[kMaxRunPieces];
   const int r_top = in_lds ? min(np_max, kMaxRunPieces) : 1;
-  {
-    const int w = tid >> 6, r = w + 1, rs = min(r * S, nmax);
-    if (r <= r_top) {  // (uniform per wavefront)
-      int full = 0, items = 0, whole = 0, sum_v = 0;
-      const bool may = r == 1 || rs <= kMaxRun || (rs == nmax && (int64_t)W1 * Hkv >= (int64_t)kWholeLoad * nmax * kPlanCUs);
-      if (may)
-        for (int i = tid & 63; i < (int)n_tiles; i += 64) {
-          const int v = nu[i], f = v / rs;
-          full += f;
-          items += f + (f * rs < v);
-          whole += v <= rs;
-          sum_v += v;
-        }
+  if (r_top > 1) {  // (uniform)
+    const int w = tid >> 6, lane = tid & 63, rs = min((w + 1) * S, nmax), g = kPlanCUs / nq;
+    int* const cnt = l_cnt + kMaxPieces + kRunBkts * w;  // (w < r_top only)
+    int shift = 0;
+    while ((rs >> shift) >= kRunBkts) ++shift;
+    if (w < r_top)  // (uniform per wavefront, as below)
+      for (int b = lane; b < kRunBkts; b += 64) cnt[b] = 0;
+    __syncthreads();
+    int full = 0, items = 0, whole = 0;
+    if (w < r_top) {
+      for (int i = lane; i < (int)n_tiles; i += 64) {
+        const int v = nu[i], f = v / rs, rest = v - f * rs;
+        full += f;
+        items += f + (rest > 0);
+        whole += v <= rs;
+        if (f) atomicAdd(&cnt[rs >> shift], f * kvq);
+        if (rest) atomicAdd(&cnt[rest >> shift], kvq);
+      }
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) {
         full += __shfl_xor(full, o);
         items += __shfl_xor(items, o);
         whole += __shfl_xor(whole, o);
-        sum_v += __shfl_xor(sum_v, o);
       }
-      const float F = (float)full * Hkv, N = (float)items * Hkv, R = N - F, len = (float)rs + kItemCost;
-      const float rounds = ceilf(F / kPlanCUs), room = rounds * kPlanCUs - F;
-      float t = fmaxf(F > 0.f ? rounds * len : (float)nmax + kItemCost,
-                      1.03f * ((float)sum_v * Hkv + kItemCost * N) / kPlanCUs);
-      if (R > room) t = fmaxf(t, fmaxf(rounds - 1.f, 0.f) * len + 2.f * ((float)rs * (1.f - room / R) + kItemCost));
-      t += kMergeCost * (float)(items - whole) * Hkv;
-      if ((tid & 63) == 0) l_est[w] = may ? t : INFINITY;
     }
+    __syncthreads();
+    if (w < r_top) {  // cnt[b] becomes the items in bucket b and longer
+      int c4[4], sum4 = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum4 += c4[q] = cnt[kRunBkts - 1 - 4 * lane - q];
+      int to = (int)wave_scan((unsigned)sum4) - sum4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) cnt[kRunBkts - 1 - 4 * lane - q] = to += c4[q];
+    }
+    __syncthreads();
+    if (w < r_top) {
+      auto length_at = [&](int rank) -> float {  // of the item at that rank of the queue, longest first
+        int b = 0;
+#pragma unroll
+        for (int o = kRunBkts / 2; o >= 1; o >>= 1)
+          if (cnt[b + o] > rank) b += o;
+        return (float)min(((b + 1) << shift) - 1, rs);
+      };
+      const int n = items * kvq;  // items of a queue
+      const bool many = n > 2 * g;
+      const int rounds = many ? min(full * kvq / g, (n - 1) / g) : 0, left = n - rounds * g;
+      const float mean = ((float)W1 * Hkv + kItemCost * (float)items * Hkv) / kPlanCUs;
+      float t = mean;
+      if (many) {
+        const bool descending = kvq == 1 && rs == nmax && nmax <= kL2Tiles;
+        const float last = (float)(descending ? nu[3 * n_tiles / 4] : rs) + kItemCost;
+        t = fmaxf(kTail * mean, (kvq == 1 ? kTailRun : 1.f) * (0.75f * mean + last));
+      }
+      if (left <= 2 * g) {
+        float latest = length_at(rounds * g) + kItemCost;
+        for (int k = lane; k < left - g; k += 64)
+          latest = fmaxf(latest, length_at((rounds + 1) * g - 1 - k) + length_at((rounds + 1) * g + k) + 2.f * kItemCost);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) latest = fmaxf(latest, __shfl_xor(latest, o));
+        t = fmaxf(t, (float)rounds * ((float)rs + kItemCost) + latest);
+      }
+      if (lane == 0) l_est[w] = t + kMergeCost * (float)(items - whole) * Hkv;
+    }
+    __syncthreads();
   }
-  __syncthreads();
   int run = 1;
+  float least = r_top > 1 ? kRunGain * l_est[0] : 0.f;
   for (int r = 2; r <= r_top; ++r)
-    if (l_est[r - 1] < l_est[run - 1]) run = r;
+    if (l_est[r - 1] < least) {
+      least = l_est[r - 1];
+      run = r;
+    }
   const int run_tiles = run * S;
   if (tid == 0) {
     const int per_q = s_base + (int)(n_tiles - n_cut) * kvq;

@@ -154,3 +154,55 @@ def test_workgroups_claim_only_where_positions_are_left(G, hkv, L, k):
             want, _ = _reference(Q[layer][:, sel.long() - cs1], K[layer], V[layer], sel, h, G)
             err = (out[layer, h].double() - want).norm() / want.norm()
             assert err <= 5e-3, (layer, h, float(err))  # bf16 probabilities and outputs: 2^-9 each
+
+
+def _estimates(nu, S, hkv):
+    """The plan's estimate of a layer launch, in key tiles, for runs of r = 1 .. 8
+    pieces (float64; lengths in buckets of 2^shift as the plan counts them)."""
+    nq = 8 if hkv % 8 == 0 else hkv if hkv in (1, 2, 4) else 1
+    kvq, g, res = hkv // nq, 256 // nq, []
+    for r in range(1, min(8, -(-nu[0] // S)) + 1):
+        rs = min(r * S, nu[0])
+        shift = 0
+        while (rs >> shift) > 255:
+            shift += 1
+        lens = sorted((x for v in nu for x in [rs] * (v // rs) + [v % rs] * (v % rs > 0) for _ in range(kvq)), reverse=True)
+        at = [min((((x >> shift) + 1) << shift) - 1, rs) for x in lens]
+        n, full = len(lens), sum(v // rs for v in nu) * kvq
+        rounds = min(full // g, (n - 1) // g) if n > 2 * g else 0
+        mean = t = (sum(nu) * hkv + 7.0 * n * nq) / 256
+        if n > 2 * g:
+            last = nu[3 * len(nu) // 4] if kvq == 1 and rs == nu[0] <= 128 else rs
+            t = max(1.05 * mean, (0.95 if kvq == 1 else 1.0) * (0.75 * mean + last + 7.0))
+        if n - rounds * g <= 2 * g:
+            at = at[rounds * g:]
+            t = max(t, rounds * (rs + 7.0) + max([at[0] + 7.0] + [at[g - 1 - k] + at[g + k] + 14.0 for k in range(len(at) - g)]))
+        res.append(t + 0.0065 * (n * nq // hkv - sum(v <= rs for v in nu)) * hkv)
+    return res
+
+
+# Whole row tiles of seven heads in one queue, and of two heads that fit an L2 or
+# do not; items paired in one round and a bit, lengths beyond 255 tiles among them;
+# a share per CU just above and below two pieces of 288 tiles.
+@pytest.mark.parametrize("G,hkv,T,k", [(4, 7, 16384, 5376), (4, 7, 12288, 5760), (8, 2, 6000, 5625), (8, 2, 16384, 8192),
+                                       (4, 8, 2048, 1920), (8, 8, 3000, 1000), (1, 8, 65536, 1000), (8, 1, 6000, 2000),
+                                       (8, 2, 65536, 6349), (8, 2, 68000, 6375), (1, 16, 3000, 2800)])
+def test_run_length_is_the_estimates_best(G, hkv, T, k):
+    from paper_2607_19547_amd import binding as b
+    log(f"case run length G={G} Hkv={hkv} T={T} k={k}")
+    cs1, hq, D = T // 16, G * hkv, 128
+    n = T - cs1
+    geo = b.Geo(1, hq, hkv, D, (16, 24, 24), "bf16", np.array([0, cs1, T], np.int64))
+    z = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device="cuda")
+    K, V, Q, KF, VF = z(1, hkv, T, D), z(1, hkv, T, D), z(1, hq, n, D), z(1, hkv, n, D), z(1, hkv, n, D)
+    sel = np.sort(np.random.default_rng(T + k).choice(n, k, replace=False)) + cs1
+    out = torch.empty((1, hq, k, D), dtype=torch.bfloat16, device="cuda")
+    ws = torch.zeros(b.selective_attend_scatter_workspace(geo, k, 1), dtype=torch.uint8, device="cuda")
+    b.selective_attend_scatter(geo, K, V, 0, 1, torch.from_numpy(sel.astype(np.int32)).cuda(), k, Q, KF, VF, out, None, ws)
+    torch.cuda.synchronize()
+    plan = ws.view(torch.int32).cpu().numpy()
+    S, run, nt = int(plan[9]), int(plan[15]), int(plan[17])
+    want = _estimates([int(v) for v in plan[HDR:HDR + nt]], S, hkv)
+    log(f"  {nt} row tiles, S {S}, run {run}, estimates {[round(x, 1) for x in want]}")
+    want[0] *= 0.99  # (runs of several pieces are taken where they gain 1%)
+    assert want[run - 1] <= min(want) * (1 + 1e-5)  # (float32 sums of a few terms: 2^-22 each)
