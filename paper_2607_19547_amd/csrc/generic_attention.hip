@@ -390,7 +390,9 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
     __syncthreads();  // (also: every wavefront is done with Q in LDS)
     float M = -INFINITY, L = 0.f;
     for (int w = 0; w < nw; ++w) M = fmaxf(M, s_m[w][q]);
-    for (int w = 0; w < nw; ++w) L += s_m[w][q] == -INFINITY ? 0.f : s_l[w][q] * expf(s_m[w][q] - M);
+    // (a part without a weight is left out; one whose scores are NaN has a max of
+    // -inf too, but a sum of NaN)
+    for (int w = 0; w < nw; ++w) L += s_l[w][q] == 0.f ? 0.f : s_l[w][q] * expf(s_m[w][q] - M);
     const float f = (m_run == -INFINITY ? 0.f : expf(m_run - M)) / L;
     if (wave == 0 && hi == 0 && g_q >= 0 && a.lse) a.lse[s_orow[q]] = M + logf(L);
 #pragma unroll

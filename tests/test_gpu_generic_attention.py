@@ -125,3 +125,28 @@ def test_rows_do_not_see_later_non_finite_rows(dtype, D, G):
         assert np.array_equal(out[:, a], clean[:, a]) and np.array_equal(lse[:, sel < t_k], clean_lse[:, sel < t_k])
         assert np.all(np.isposinf(got[:, m, 5])) and np.array_equal(np.delete(got[:, m], 5, 2), np.delete(want[:, m], 5, 2))
         assert np.all(np.isnan(got[:, z]))
+
+
+@pytest.mark.parametrize("dtype,D,G", [("f32", 128, 2), ("bf16", 64, 3), ("f32", 258, 1), ("f32", 16, 4)])
+def test_nan_scores_reach_the_log_sum_exp(dtype, D, G):
+    """A query of NaN, and a tile of NaN keys that is all one wavefront sees: the
+    rows' results and log-sum-exps are NaN, and every other row keeps its bits."""
+    log(f"case NaN scores {dtype} D={D} G={G}")
+    geo, cs, x, sel = _make(dtype, D, G, 1, (96, 160), 0.5, seed=5)
+    cs1 = int(cs[1])
+    clean, clean_lse = _call(geo, cs, dtype, x, sel, False)
+    nan = np.uint16(0x7fc0) if dtype == "bf16" else np.float32(np.nan)
+    q_nan = int(sel[3])
+    assert q_nan < 128 and (sel >= 160).any() and (sel < 128).sum() > 4
+    x["Q"][0, 0, q_nan - cs1, 0] = nan
+    x["K"][0, 0, 128:160, :] = nan  # (32-key tiles, eight wavefronts: the fifth one's only tile)
+    x["KF"][0, 0, 128 - cs1:160 - cs1, :] = nan
+    for paged in (False, True):
+        out, lse = _call(geo, cs, dtype, x, sel, paged)
+        got = _dec(out, dtype)
+        bad = np.zeros(lse.shape, bool)
+        bad[:, sel >= 128] = True
+        bad[0, sel == q_nan] = True
+        assert np.isnan(lse[bad]).all(), lse[bad][~np.isnan(lse[bad])]
+        assert np.isnan(got[bad]).all()
+        assert np.array_equal(lse[~bad], clean_lse[~bad]) and np.array_equal(out[~bad], clean[~bad])
