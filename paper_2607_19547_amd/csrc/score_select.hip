@@ -11,6 +11,8 @@
 // threshold and the lowest-index ties at it) are compacted in index order, so
 // the output is ascending and exactly k long.  All counts are order
 // independent, so the result is deterministic.
+#include <type_traits>
+
 #include "cs_common.h"
 
 namespace cs {
@@ -216,7 +218,14 @@ __device__ __forceinline__ void find_digit(const unsigned* hist, unsigned kk, un
 // instructions) and passes over memory for the lower digits take 102 us for
 // 260,096; the four-digit form with a histogram per wavefront and one load in
 // flight, which this replaced, took 335 us (48 us for 63,488, held in
-// registers).
+// registers).  A band that holds more than the list (scores of which many
+// per cent lie within a few per cent of the k-th) is found out by pass 2, and
+// the histogram comes on top; from about 340,000 candidates at k = n / 2 (490,000
+// at n / 10) on the list is too short for the sample's band, and the histogram
+// comes at once.  Score and selection together, one head of D = 2, 260,096
+// candidates, k = n / 10: 100 us for log-normal scores, 209 for norms of 256
+// normal draws, 230 for equal scores; 500,000 candidates 299, 336, 369 (the form
+// replaced: 386, 313, 334; 735, 598, 636).
 __global__ __launch_bounds__(kSelThreads) void radix_select_topk(const float* __restrict__ scores, int n, int k,
                                                                  int cs1, int ng, int32_t* __restrict__ sel) {
   constexpr int kHist = kSelBins * kSelCopies + kSelBins / 4;  // words of the first digit's histogram, padding included
@@ -281,6 +290,18 @@ __global__ __launch_bounds__(kSelThreads) void radix_select_topk(const float* __
     for (int b = tid; b < words / 4; b += kSelThreads) ((u32x4*)hist)[b] = u32x4{0u, 0u, 0u, 0u};
   };
   const int copy = lane & (kSelCopies - 1);
+  // Whether a group's scores are all alike from bit `shift` up (*d0), so that one
+  // add counts them: adds to one bin go through one by one.  Asked only where
+  // every score sampled has the same first digit (260,096 equal scores: 230 us
+  // with it, 340 without).
+  bool crowded = false;
+  auto one_digit = [&](const u32x4& u, int shift, unsigned* d0) -> bool {
+    *d0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(u[0] >> shift));  // (lane 0 holds a score)
+    bool same = true;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) same &= u[e] >> shift == *d0;
+    return __ballot(same) == ~0ull;
+  };
 
   // 1. the sample and the band [lo, hi)
   const int stride = (n + kSelSample - 1) / kSelSample, ns = (n + stride - 1) / stride;
@@ -315,6 +336,7 @@ __global__ __launch_bounds__(kSelThreads) void radix_select_topk(const float* __
     const int r_hi = stride == 1 ? k : max(1, r - delta), r_lo = stride == 1 ? k : max(r_hi, min(ns - 1, r + delta));
     const unsigned ranks[2] = {(unsigned)r_hi, (unsigned)r_lo};
     find_digits<kSelBins, kSelCopies, 2>(hist, ranks, tot, res);
+    crowded = res[0].in == (unsigned)ns;
     unsigned hi = (res[0].digit + 1u) << kSelShift;
     lo = res[1].digit << kSelShift;
     // the band's width fits a list entry, and it reaches past the sample's
@@ -410,11 +432,23 @@ __global__ __launch_bounds__(kSelThreads) void radix_select_topk(const float* __
     clear(kHist);
     if (tid < kSelWaves * kSelParts) seg[tid] = 0;
     __syncthreads();
-    visit(0, ng, [&](const u32x4& u, int, int) {
+    // (two loops each: a test in the usual one costs it 5%)
+    auto first_digits = [&](auto alike) {
+      visit(0, ng, [&](const u32x4& u, int, int) {
+        if constexpr (decltype(alike)::value) {
+          unsigned d0;
+          if (one_digit(u, kSelShift, &d0)) {
+            if (lane == 0) atomicAdd(&hist[hist_at<kSelBins, kSelCopies>(d0)], (unsigned)kSelGroup);
+            return;
+          }
+        }
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if ((int)u[e] >= 0) atomicAdd(&hist[hist_at<kSelBins, kSelCopies>(u[e] >> kSelShift) + copy], 1u);
-    });
+        for (int e = 0; e < 4; ++e)
+          if ((int)u[e] >= 0) atomicAdd(&hist[hist_at<kSelBins, kSelCopies>(u[e] >> kSelShift) + copy], 1u);
+      });
+    };
+    if (crowded) first_digits(std::true_type{});  // (uniform)
+    else first_digits(std::false_type{});
     __syncthreads();
     find_digit<kSelBins, kSelCopies>(hist, (unsigned)k, tot, res);
     thr = res[0].digit;
@@ -425,11 +459,22 @@ __global__ __launch_bounds__(kSelThreads) void radix_select_topk(const float* __
       below -= w;
       clear(2048 * 8);
       __syncthreads();
-      visit(0, ng, [&](const u32x4& u, int, int) {
+      auto lower_digits = [&](auto alike) {
+        visit(0, ng, [&](const u32x4& u, int, int) {
+          if constexpr (decltype(alike)::value) {
+            unsigned d0;
+            if (one_digit(u, below, &d0)) {
+              if (lane == 0 && d0 >> w == thr) atomicAdd(&hist[(d0 & ((1u << w) - 1u)) * 8], (unsigned)kSelGroup);
+              return;
+            }
+          }
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (u[e] >> up == thr) atomicAdd(&hist[((u[e] >> below) & ((1u << w) - 1u)) * 8 + (lane & 7)], 1u);
-      });
+          for (int e = 0; e < 4; ++e)
+            if (u[e] >> up == thr) atomicAdd(&hist[((u[e] >> below) & ((1u << w) - 1u)) * 8 + (lane & 7)], 1u);
+        });
+      };
+      if (crowded) lower_digits(std::true_type{});
+      else lower_digits(std::false_type{});
       __syncthreads();
       find_digit<2048, 8>(hist, kk, tot, res);
       thr = thr << w | res[0].digit;

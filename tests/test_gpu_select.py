@@ -56,3 +56,10 @@ def test_selection_of_given_scores(n, kind):
             assert np.array_equal(scores.cpu().numpy(), want)
             s = sel.cpu().numpy()
             assert s[k] == -7 and np.array_equal(s[:k], oracle.select.select_top(want, k, cs1)), k
+
+
+@pytest.mark.parametrize("kind", ["spread", "equal", "close", "mixed"])
+def test_selection_beyond_the_listed_band(kind):
+    """More candidates than a band of the sample's width fits the list for: the
+    histogram of every score from the start, or after the list overflows."""
+    test_selection_of_given_scores(500_001, kind)
