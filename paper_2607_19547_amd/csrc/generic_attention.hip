@@ -16,20 +16,28 @@
 // products (kGroups groups per tile and operand, at most 32 registers each).
 //
 // Bound: the float32 matrix rate (256 flop per clock and CU, twice what plain
-// FMAs reach).  A key tile costs D/2 + 16 ceil(D/32) matrix instructions of 64
-// cycles per wavefront; the loads (16 + 16 ceil(D/32) instructions at D = 128)
-// stay below a quarter of that time in the address units, and K/V need 1/8 of
-// the L1 rate, so LDS staging would add barriers and save nothing.
+// FMAs reach).  A key tile costs 32 NB matrix instructions of 64 cycles per
+// wavefront, half of them per product, where NB is the instance's blocks of 32
+// elements (1, 2, 3, 4, 6, 8, 10, 12 or 16: D rounds up to one of them); the
+// loads (16 + 16 NB instructions at D = 128) stay below a quarter of that time in
+// the address units, and K/V need 1/8 of the L1 rate, so LDS staging would add
+// barriers and save nothing.  Above D = 192 the instances spill (about 120 to 140
+// registers with 8 blocks, 240 with 10, 500 with 12, outside most of the
+// products; 1,140 to 1,250 with 16, whose accumulators, O and a tile of S, are more
+// than the 256 accumulation registers, so that every group of products moves
+// some of them).
 //
 // Measured (4,096 float32 tokens, 512 selected rows, 16 query heads, 2 KV heads,
-// D = 128, scatter included): 167 us, 77 TFLOP/s, against 2,870 us for one
-// wavefront per (row, head) with scalar FMAs, which it replaces at every
-// geometry (bf16 D = 64: 107 against 960 us; D = 512: 772 against 4,288 us; 64
-// tokens of D = 16: 13 against 17 us).  The error against float64 is 5.6e-7 to
-// 9.8e-7 over eight inputs, against 7.5e-7 to 1.1e-6 (shorter sums).  The
-// longest row tile sets the time when there are about as many workgroups as CUs
-// (there 4,096 keys against 3,072 on average); splitting it further would need
-// a workspace, which these calls do not take.
+// D = 128, scatter included): 163 us, 79 TFLOP/s, against 2,870 us for one
+// wavefront per (row, head) with scalar FMAs, which it replaces (but for the
+// shortest caches, see sel_attn_row).  The same layer, calls replayed back to
+// back: float32 D = 128 186 against 2,874 us; bf16 D = 64 120 against 1,448; float32
+// D = 320 448 against 6,529 and D = 512 1,629 against 10,095; 96 tokens of D = 258 38
+// against 66, 64 tokens of D = 16 (4 query heads) 8.7 against 18.7.  The error
+// against float64 is 5.6e-7 to 9.8e-7 over eight inputs, against 7.5e-7 to 1.1e-6
+// (shorter sums).  The longest row tile sets the time when there are about as
+// many workgroups as CUs (there 4,096 keys against 3,072 on average); splitting
+// it further would need a workspace, which these calls do not take.
 #include <math.h>
 
 #include <algorithm>
@@ -51,8 +59,10 @@ struct GenAttnArgs {
 
 constexpr int kGenQ = 32;       // query vectors per workgroup
 constexpr int kGenKeys = 32;    // keys per tile
-// Wavefronts per workgroup, at most: eight (two per SIMD, 256 registers each),
-// four where the accumulators alone need most of that.
+// Wavefronts per workgroup: eight (two per SIMD, 256 registers each), four where
+// the accumulators alone need most of that.  A short cache has fewer key tiles;
+// its other wavefronts share the loading of Q and the writing of the results
+// (32 tokens, float32 D = 128: 16 us with eight wavefronts, 27 to 32 with one).
 constexpr int gen_waves(int nb) { return nb <= 4 ? 8 : 4; }
 constexpr int kGenBufW = 33;    // row stride (floats) of the merge buffer
 constexpr int64_t kGenGridX = 1 << 22;
@@ -159,24 +169,24 @@ struct GenTile<PagedRowsT<CAP>> {
 // NB: 32-element blocks of the head dimension, D <= 32 NB.
 template <typename E, int NB, typename Rows>
 __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const GenAttnArgs a, const Rows rows) {
-  constexpr int kWavesMax = gen_waves(NB);
+  constexpr int nw = gen_waves(NB), kThreads = 64 * nw;
   constexpr int kGroups = NB <= 2 ? 1 : NB <= 4 ? 2 : NB <= 8 ? 4 : 8;  // load groups per tile, for K and for V
   constexpr int kSteps = 4 * NB / kGroups;   // K chunks per lane and group (each lane half takes every other chunk)
   constexpr int kVRows = 16 / kGroups;       // V rows per lane and group
   constexpr int kQW = 32 * NB + 4;           // Q row stride in LDS (floats): four pad words spread the banks
-  constexpr int kMinD = NB <= 4 ? 32 * (NB - 1) : NB <= 8 ? 32 * (NB - 2) : 256;  // D > kMinD
+  constexpr int kMinD = NB <= 4 ? 32 * (NB - 1) : NB <= 12 ? 32 * (NB - 2) : 384;  // D > kMinD
   constexpr int ES = sizeof(E);
   typedef GenLoad<E> Ld;
   typedef typename Ld::chunk chunk;
   typedef typename Ld::elem elem;
-  __shared__ __attribute__((aligned(16))) float lds[kGenQ * kQW > kWavesMax * kGenQ * kGenBufW ? kGenQ * kQW : kWavesMax * kGenQ * kGenBufW];
-  __shared__ float s_m[kWavesMax][kGenQ], s_l[kWavesMax][kGenQ];
+  constexpr int kLds = kGenQ * kQW > nw * kGenQ * kGenBufW ? kGenQ * kQW : nw * kGenQ * kGenBufW;
+  __shared__ __attribute__((aligned(16))) float lds[kLds];  // Q, later the parts of the results
+  __shared__ float s_m[nw][kGenQ], s_l[nw][kGenQ];
   __shared__ int s_tok[kGenQ];
   // rows of a.q and of the results that the query vectors have (the 64-bit
   // divisions behind them once per vector; once per element they took 1.3 us of
   // a 168 us layer and about as much of the 64-token composition)
   __shared__ int64_t s_qrow[kGenQ], s_orow[kGenQ];
-  const int nw = blockDim.x >> 6;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane & 31, hi = lane >> 5;
   const int layer = a.lb + blockIdx.z;
@@ -195,17 +205,33 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
       const int h = kv * G + (int)(x0 + tid - m * G);
       int t = -1;
       if (m < a.n_sel) t = a.sel[m];
-      s_tok[tid] = t >= a.cs1 && t < a.T ? t : -1;  // out-of-contract index: no output
-      s_qrow[tid] = a.q_by_slot ? ((int64_t)blockIdx.z * a.Hq + h) * a.n_sel + m
-                                : ((int64_t)layer * a.Hq + h) * a.n + (t - a.cs1);
+      const bool ok = t >= a.cs1 && t < a.T;  // out-of-contract index: no output
+      s_tok[tid] = ok ? t : -1;
+      s_qrow[tid] = !ok ? 0  // (loaded, not used)
+                    : a.q_by_slot ? ((int64_t)blockIdx.z * a.Hq + h) * a.n_sel + m
+                                  : ((int64_t)layer * a.Hq + h) * a.n + (t - a.cs1);
       s_orow[tid] = ((int64_t)layer * a.Hq + h) * a.n_sel + m;
     }
     __syncthreads();
-    for (int i = tid; i < kGenQ * 32 * NB; i += blockDim.x) {
-      const int r = i / (32 * NB), d = i - r * (32 * NB);
-      float v = 0.f;
-      if (s_tok[r] >= 0 && d < D) v = gen_value(((const E*)a.q)[s_qrow[r] * D + d]);
-      lds[r * kQW + d] = v;
+    // Q into LDS, up to eight loads in flight per thread (loaded one by one, 32
+    // rows of 512 elements took 64 round trips, most of a short cache's time)
+    constexpr int kQPer = kGenQ * 32 * NB / kThreads, kQBatch = kQPer < 8 ? kQPer : 8;
+    static_assert(kQPer % kQBatch == 0, "whole batches");
+    int tq = tid;  // (opaque: its indices are not kept for the results)
+    asm volatile("" : "+v"(tq));
+#pragma unroll 1
+    for (int k0 = 0; k0 < kQPer; k0 += kQBatch) {
+      E v[kQBatch];
+#pragma unroll
+      for (int k = 0; k < kQBatch; ++k) {
+        const int i = tq + (k0 + k) * kThreads, r = i / (32 * NB), d = i - r * (32 * NB);
+        v[k] = ((const E*)a.q)[s_qrow[r] * D + min(d, D - 1)];
+      }
+#pragma unroll
+      for (int k = 0; k < kQBatch; ++k) {
+        const int i = tq + (k0 + k) * kThreads, r = i / (32 * NB), d = i - r * (32 * NB);
+        lds[r * kQW + d] = s_tok[r] >= 0 && d < D ? gen_value(v[k]) : 0.f;
+      }
     }
     __syncthreads();
     const int g_q = s_tok[q];
@@ -380,8 +406,9 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
       }
     }
 
-    // merge the wavefronts' parts: weights from the overall max, then the
-    // head dimension 32 elements at a time
+    // merge the wavefronts' parts (of those that have a key tile): weights from
+    // the overall max, then the head dimension 32 elements at a time
+    const int nk = min(nw, g_max / kGenKeys + 1);
     l_run = half_sum(l_run);
     if (hi == 0) {
       s_m[wave][q] = m_run;
@@ -389,24 +416,28 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
     }
     __syncthreads();  // (also: every wavefront is done with Q in LDS)
     float M = -INFINITY, L = 0.f;
-    for (int w = 0; w < nw; ++w) M = fmaxf(M, s_m[w][q]);
+    for (int w = 0; w < nk; ++w) M = fmaxf(M, s_m[w][q]);
     // (a part without a weight is left out; one whose scores are NaN has a max of
     // -inf too, but a sum of NaN)
-    for (int w = 0; w < nw; ++w) L += s_l[w][q] == 0.f ? 0.f : s_l[w][q] * expf(s_m[w][q] - M);
+    for (int w = 0; w < nk; ++w) L += s_l[w][q] == 0.f ? 0.f : s_l[w][q] * expf(s_m[w][q] - M);
     const float f = (m_run == -INFINITY ? 0.f : expf(m_run - M)) / L;
     if (wave == 0 && hi == 0 && g_q >= 0 && a.lse) a.lse[s_orow[q]] = M + logf(L);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       if (32 * j < D) {  // (uniform)
+        if (wave < nk) {  // (uniform)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          lds[(wave * kGenQ + q) * kGenBufW + 8 * (r >> 2) + 4 * hi + (r & 3)] = o[j][r] * f;
+          for (int r = 0; r < 16; ++r)
+            lds[(wave * kGenQ + q) * kGenBufW + 8 * (r >> 2) + 4 * hi + (r & 3)] = o[j][r] * f;
+        }
         __syncthreads();
-        for (int i = tid; i < kGenQ * 32; i += blockDim.x) {
+        int tr = tid;
+        asm volatile("" : "+v"(tr));
+        for (int i = tr; i < kGenQ * 32; i += kThreads) {
           const int r = i >> 5, d = 32 * j + (i & 31);
           if (d < D && s_tok[r] >= 0) {
             float v = 0.f;
-            for (int w = 0; w < nw; ++w) v += lds[(w * kGenQ + r) * kGenBufW + (i & 31)];
+            for (int w = 0; w < nk; ++w) v += lds[(w * kGenQ + r) * kGenBufW + (i & 31)];
             gen_store((E*)a.out + s_orow[r] * D + d, v);
           }
         }
@@ -414,6 +445,62 @@ __global__ __launch_bounds__(64 * gen_waves(NB)) void sel_attn_generic(const Gen
       }
     }
   }
+}
+
+// Caches of one or two key tiles: one wavefront per (row, query head), a lane per
+// key for the scores and per element for the sums.  The tile kernel would leave
+// the work to one or two wavefronts, whose loads and products then follow one
+// another, whatever the number of keys; here every row has its own, and the time
+// grows with the keys.  Up to 24 keys for rows of at most 128 elements, 40 for
+// 384, 64 beyond (where the tile kernel spills most).  Measured, one layer, a
+// fifth of the rows, time over the tile kernel's at 20, 28, 40, 56 and 64 keys: D =
+// 16: 0.98, 1.21, 1.35, 1.70, 1.91; D = 128: 0.85, 0.88, 1.21, 1.47, 1.60; D = 256:
+// 0.67, 0.83, 0.97, 1.29, 1.37; D = 512: 0.45, 0.57, 0.72, 0.92, 1.02 (8 to 80 us a
+// layer; with nine tenths of the rows the lines would lie at two thirds of these).
+static bool one_row_kernel(int64_t T, int D) { return T <= (D <= 128 ? 24 : D <= 384 ? 40 : 64); }
+template <typename E, typename Rows>
+__global__ __launch_bounds__(64) void sel_attn_row(const GenAttnArgs a, const Rows rows) {
+  __shared__ float qs[512], ps[64];
+  const int64_t m = blockIdx.x;
+  const int h = blockIdx.y, kv = h / a.G, layer = a.lb + blockIdx.z, lane = threadIdx.x;
+  const int t = a.sel[m];
+  if (t < a.cs1 || t >= a.T) return;  // out-of-contract index: no output
+  const E* qp = (const E*)a.q + (a.q_by_slot ? ((int64_t)blockIdx.z * a.Hq + h) * a.n_sel + m
+                                             : ((int64_t)layer * a.Hq + h) * a.n + (t - a.cs1)) * a.D;
+  const int64_t plane = (int64_t)layer * a.Hkv + kv;
+  const int rb = a.D * (int)sizeof(E);
+  for (int d = lane; d < a.D; d += 64) qs[d] = gen_value(qp[d]);
+  __syncthreads();
+  float s = -INFINITY;  // (T <= 64: every key has a lane)
+  if (lane <= t) {
+    const E* kr = (const E*)rows.row(false, plane, lane, rb);
+    float dot = 0.f;
+    for (int d = 0; d < a.D; ++d) dot = fmaf(qs[d], gen_value(kr[d]), dot);
+    s = dot * a.scale;
+  }
+  float top = s;
+#pragma unroll
+  for (int o = 32; o; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+  const float p = lane <= t ? expf(s - top) : 0.f;
+  float sum = p;
+#pragma unroll
+  for (int o = 32; o; o >>= 1) sum += __shfl_xor(sum, o);
+  ps[lane] = p;
+  __syncthreads();
+  float acc[8] = {};
+  for (int j = 0; j <= t; ++j) {
+    const float pj = ps[j];
+    const E* vr = (const E*)rows.row(true, plane, j, rb);
+#pragma unroll
+    for (int x = 0; x < 8; ++x)
+      if (lane + 64 * x < a.D) acc[x] = fmaf(pj, gen_value(vr[lane + 64 * x]), acc[x]);
+  }
+  const int64_t orow = ((int64_t)layer * a.Hq + h) * a.n_sel + m;
+  const float inv = 1.f / sum;
+#pragma unroll
+  for (int x = 0; x < 8; ++x)
+    if (lane + 64 * x < a.D) gen_store((E*)a.out + orow * a.D + lane + 64 * x, acc[x] * inv);
+  if (a.lse && lane == 0) a.lse[orow] = top + logf(sum);
 }
 
 template <typename E, typename Rows>
@@ -426,18 +513,22 @@ static void launch_generic_e(const GenAttnArgs& a, const Rows& rows, dim3 grid, 
   else if (nb <= 4) CS_LAUNCH(tr, (sel_attn_generic<E, 4, Rows>), grid, block, 0, s, a, rows);
   else if (nb <= 6) CS_LAUNCH(tr, (sel_attn_generic<E, 6, Rows>), grid, block, 0, s, a, rows);
   else if (nb <= 8) CS_LAUNCH(tr, (sel_attn_generic<E, 8, Rows>), grid, block, 0, s, a, rows);
+  else if (nb <= 10) CS_LAUNCH(tr, (sel_attn_generic<E, 10, Rows>), grid, block, 0, s, a, rows);
+  else if (nb <= 12) CS_LAUNCH(tr, (sel_attn_generic<E, 12, Rows>), grid, block, 0, s, a, rows);
   else CS_LAUNCH(tr, (sel_attn_generic<E, 16, Rows>), grid, block, 0, s, a, rows);
 }
 
 template <typename Rows>
 static void launch_generic(const Geo& g, const GenAttnArgs& a, const Rows& rows, int layers, hipStream_t s) {
   static_assert(sizeof(GenAttnArgs) + sizeof(Rows) <= 4096, "kernel arguments within 4 KB");
-  // a wavefront for every key tile of the cache, up to the kernel's most
-  const int most = gen_waves((g.D + 31) / 32);
-  const int64_t key_tiles = (g.T + kGenKeys - 1) / kGenKeys;
-  int waves = 1;
-  while (waves < most && waves < key_tiles) waves *= 2;
-  const dim3 grid((unsigned)std::min<int64_t>(a.n_tiles * g.Hkv, kGenGridX), 1, layers), block(64 * waves);
+  if (one_row_kernel(g.T, g.D)) {
+    TraceScope tr("sel_attn_row", s);
+    const dim3 grid((unsigned)a.n_sel, g.Hq, layers);
+    if (g.dtype == CS_BF16) CS_LAUNCH(tr, (sel_attn_row<uint16_t, Rows>), grid, dim3(64), 0, s, a, rows);
+    else CS_LAUNCH(tr, (sel_attn_row<float, Rows>), grid, dim3(64), 0, s, a, rows);
+    return;
+  }
+  const dim3 grid((unsigned)std::min<int64_t>(a.n_tiles * g.Hkv, kGenGridX), 1, layers), block(64 * gen_waves((g.D + 31) / 32));
   TraceScope tr("sel_attn_generic", s);
   if (g.dtype == CS_BF16) launch_generic_e<uint16_t>(a, rows, grid, block, tr, s);
   else launch_generic_e<float>(a, rows, grid, block, tr, s);
@@ -447,6 +538,9 @@ cs_status launch_attention_generic(const Geo& g, const CacheView& cv, int lb, in
                                    int64_t n_sel, const void* qf, bool q_by_slot, void* out, float* lse,
                                    hipStream_t s, bool check_only) {
   const int layers = le - lb;
+  // the launch of a wavefront per row; the tile kernel's workgroups (at most
+  // kGenGridX x layers, of 512 threads at most) are within the limits where it is
+  static_assert(kGenGridX * 512 < int64_t(1) << 32, "work-items along x");
   const cs_status st = check_grid(n_sel, g.Hq, layers, 64, "selective attention");
   if (st || check_only) return st;
   GenAttnArgs a;

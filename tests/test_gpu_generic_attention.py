@@ -102,6 +102,18 @@ def test_generic_attention_against_oracle(dtype, D, G, Hkv, lens, rho):
         assert np.array_equal(out_p, out) and np.array_equal(lse_p, lse)
 
 
+# Caches of one and of two key tiles, either side of where a wavefront takes one
+# row (24, 40 and 64 tokens for D up to 128, 384 and beyond), and the instances
+# for 10, 12 and 16 blocks of the head dimension.
+@pytest.mark.parametrize("dtype,D,G,Hkv,lens", [("f32", 2, 3, 1, (1, 1)), ("f32", 128, 4, 1, (5, 19)), ("f32", 128, 4, 1, (5, 20)),
+                                                ("bf16", 64, 3, 2, (1, 23)), ("f32", 130, 3, 2, (5, 35)), ("f32", 130, 3, 2, (5, 36)),
+                                                ("bf16", 384, 2, 2, (20, 20)), ("bf16", 384, 2, 2, (20, 21)), ("f32", 512, 2, 2, (1, 63)),
+                                                ("f32", 512, 2, 2, (1, 64)), ("bf16", 386, 7, 1, (16, 15, 33)), ("bf16", 386, 7, 1, (16, 15, 34)),
+                                                ("bf16", 318, 2, 1, (30, 34)), ("f32", 322, 1, 2, (30, 93)), ("f32", 384, 2, 1, (70, 141))])
+def test_short_caches_and_wide_rows(dtype, D, G, Hkv, lens):
+    test_generic_attention_against_oracle(dtype, D, G, Hkv, lens, 0.6)
+
+
 @pytest.mark.parametrize("dtype,D,G", [("f32", 128, 2), ("bf16", 64, 3), ("f32", 20, 1)])
 def test_rows_do_not_see_later_non_finite_rows(dtype, D, G):
     """Cache rows after a row's token never reach it, whatever they hold; the rows
