@@ -309,19 +309,15 @@ __host__ __device__ inline int n_queues(int Hkv) {
   return Hkv % kXcds == 0 ? kXcds : (Hkv == 1 || Hkv == 2 || Hkv == 4 ? Hkv : 1);
 }
 
-// Sum or max over the 1024 threads of the planning workgroup (every thread
-// gets the result).
-__device__ __forceinline__ int block_reduce(int v, bool is_max, int* red) {
+// Sum over the 1024 threads of the planning workgroup (every thread gets it).
+__device__ __forceinline__ int block_reduce(int v, int* red) {
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const int y = __shfl_xor(v, o);
-    v = is_max ? max(v, y) : v + y;
-  }
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
   __syncthreads();  // red may still be read by the previous call
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  int r = red[0];
-  for (int w = 1; w < 16; ++w) r = is_max ? max(r, red[w]) : r + red[w];
+  int r = 0;
+  for (int w = 0; w < 16; ++w) r += red[w];
   return r;
 }
 
@@ -503,7 +499,7 @@ __device__ void plan_body(const PlanArgs& p) {
       return;
     }
   }
-  const int W1 = block_reduce(sum, false, red);
+  const int W1 = block_reduce(sum, red);
   // piece size: about kItemsPerCU items per CU, raised until the partial
   // slots fit in part_cap (no cut at all always fits)
   const int64_t per = (int64_t)kPlanCUs * kItemsPerCU;
@@ -525,7 +521,7 @@ __device__ void plan_body(const PlanArgs& p) {
           const int v = nu[i];
           if (v > Sk) loc += (v + Sk - 1) / Sk;
         }
-        if ((int64_t)block_reduce(loc, false, red) * Hkv <= part_cap) {
+        if ((int64_t)block_reduce(loc, red) * Hkv <= part_cap) {
           S = Sk;
           break;
         }
@@ -745,7 +741,7 @@ __device__ void plan_body(const PlanArgs& p) {
     if (tid < 256) l_bkt[tid] = 0;
     int loc = 0;
     for (int i = tid; i < (int)n_tiles; i += 1024) loc += (nsp[i] + run - 1) / run * kvq;
-    n_runs = block_reduce(loc, false, red);
+    n_runs = block_reduce(loc, red);
     const int l0 = n_runs * nq <= 2 * kPlanCUs ? 0 : n_runs - (n_runs + 3) / 4;
     const bool sorted = n_runs - l0 <= kPlanSortCap;
     int4* const out = (int4*)(plan + p.run_off);
