@@ -206,3 +206,53 @@ def test_run_length_is_the_estimates_best(G, hkv, T, k):
     log(f"  {nt} row tiles, S {S}, run {run}, estimates {[round(x, 1) for x in want]}")
     want[0] *= 0.99  # (runs of several pieces are taken where they gain 1%)
     assert want[run - 1] <= min(want) * (1 + 1e-5)  # (float32 sums of a few terms: 2^-22 each)
+
+
+@pytest.mark.parametrize("where", ["descriptor", "count", "offset", "checksum"])
+def test_damaged_runs_are_replanned(where):
+    """The second pair of checksum words covers the runs: recomputed on the host, and
+    a kept plan with one int of a run descriptor, the count of runs, the offset of
+    their descriptors or the sum itself changed is made again, with the outputs
+    of an undamaged one."""
+    from paper_2607_19547_amd import binding as b
+    log(f"case damaged runs: {where}")
+    G, hkv, T, k, L, D = 1, 8, 12000, 1500, 2, 128
+    cs1 = T // 16
+    n, hq = T - cs1, G * hkv
+    geo = b.Geo(L, hq, hkv, D, (16, 24, 24), "bf16", np.array([0, cs1, T], np.int64))
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=gen).to(torch.bfloat16)
+    K, V, Q, KF, VF = r(L, hkv, T, D), r(L, hkv, T, D), r(L, hq, n, D), r(L, hkv, n, D), r(L, hkv, n, D)
+    sel = (torch.randperm(n, device="cuda", generator=gen)[:k].sort().values + cs1).to(torch.int32)
+    out, lse = torch.zeros((L, hq, k, D), dtype=torch.bfloat16, device="cuda"), torch.zeros((L, hq, k), device="cuda")
+    ws = torch.zeros(b.selective_attend_scatter_workspace(geo, k, 1), dtype=torch.uint8, device="cuda")
+    call = lambda layer, o, l, w: b.selective_attend_scatter(geo, K, V, layer, layer + 1, sel, k, Q, KF, VF, o, l, w)
+    call(0, out, lse, ws)
+    torch.cuda.synchronize()
+    plan = ws.view(torch.int32)
+    host = plan.cpu().numpy()
+    per_q, off, run, n_runs, ro = (int(host[i]) for i in (12, 14, 15, 25, 26))
+    assert run >= 2 and ro != off, "the case is one with runs of several pieces"
+    idx = np.concatenate([[25, 26], np.arange(ro, ro + 4 * n_runs)]).astype(np.uint64)
+    v, m32 = host.view(np.uint32)[idx.astype(np.int64)].astype(np.uint64), np.uint64(0xFFFFFFFF)
+    c1 = int(np.sum((v * (2 * idx + 1)) & m32) & m32)
+    c2 = int(np.sum((((v ^ ((idx * 0x9E3779B9) & m32)) * 0x85EBCA6B) & m32) + idx) & m32)
+    assert (c1, c2) == (int(np.uint32(host[27])), int(np.uint32(host[28])))
+    call(1, out, lse, ws)
+    torch.cuda.synchronize()
+    assert int(plan[24]) == 1, "undamaged, the plan is kept"
+    want_out, want_lse = out[1].clone(), lse[1].clone()
+    if where == "descriptor":
+        plan[ro + 4 * (n_runs // 2) + 3] -= 1  # a run that ends a key tile early
+    elif where == "count":
+        plan[25] -= 1
+    elif where == "offset":
+        plan[26] = off  # the piece descriptors, also within the plan
+    else:
+        plan[28] += 1
+    out[1].zero_()
+    lse[1].zero_()
+    call(1, out, lse, ws)
+    torch.cuda.synchronize()
+    assert int(plan[24]) == 0, "made again"
+    assert torch.equal(out[1], want_out) and torch.equal(lse[1], want_lse)
