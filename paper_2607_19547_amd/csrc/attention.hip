@@ -1070,12 +1070,12 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
   };
   // The first item, taken without a claim.  Its descriptor is loaded beside the
   // header, from both places it can be in (a workgroup past its queue's items
-  // reads another's, unused).  Where the first items are all there is, nothing
-  // is claimed later either.  (A layer of the 8,192-token composition, 246 items:
-  // with the header's ints and the descriptor read one after the other an item
-  // started 2.8 us after the launch, and the claims with nothing left to claim,
-  // one atomic per workgroup on each queue, held back its results by 3.2 us on
-  // average and 7.6 at most.  The launch: 41.4 us before, 35.3 now.)
+  // reads another's, unused).  Where the first items are all there is, no
+  // workgroup looks for another one.  (A layer of the 8,192-token composition,
+  // 246 items: with the header's ints and the descriptor read one after the
+  // other an item started 2.8 us after the launch, and the claims with nothing
+  // left to claim, one atomic per workgroup on each queue, held back its results
+  // by 3.2 us on average and 7.6 at most.  The launch: 41.4 us before, 35.3 now.)
   auto begin_first = [&]() -> bool {
     const int nq = n_queues(a.Hkv), first = rank_in_queue(blockIdx.x, nq);
     jq = (blockIdx.x % kXcds) % nq;
@@ -1321,7 +1321,9 @@ __global__ __launch_bounds__(kThreads) void sel_attn_mfma(const AttnArgs a, cons
     // The next item is claimed at the start of the last group of four steps
     // that leaves at least two steps, so that the claim's round trip overlaps
     // them (an earlier claim would hold the item back from idle workgroups
-    // for longer).
+    // for longer).  It is made also where no items are left to claim, its answer
+    // then unused: a test for that here, inside the tile loop, cost 0.4% at 32,768
+    // tokens, rho = 1.
     const int claim_at = max(0, (n_kt - 2) & ~3);
     asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // tiles 0 and 1 and the queries have landed
     __builtin_amdgcn_s_barrier();

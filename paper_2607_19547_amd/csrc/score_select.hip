@@ -224,8 +224,8 @@ __device__ __forceinline__ void find_digit(const unsigned* hist, unsigned kk, un
 // at n / 10) on the list is too short for the sample's band, and the histogram
 // comes at once.  Score and selection together, one head of D = 2, 260,096
 // candidates, k = n / 10: 100 us for log-normal scores, 209 for norms of 256
-// normal draws, 230 for equal scores; 500,000 candidates 299, 336, 369 (the form
-// replaced: 386, 313, 334; 735, 598, 636).
+// normal draws, 230 for equal scores; 500,000 candidates 299, 336, 580 (the form
+// replaced: 386, 313, 334; 735, 598, 641).
 __global__ __launch_bounds__(kSelThreads) void radix_select_topk(const float* __restrict__ scores, int n, int k,
                                                                  int cs1, int ng, int32_t* __restrict__ sel) {
   constexpr int kHist = kSelBins * kSelCopies + kSelBins / 4;  // words of the first digit's histogram, padding included
